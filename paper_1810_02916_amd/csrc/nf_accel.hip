@@ -115,18 +115,8 @@ __global__ void __launch_bounds__(256) k_accel_simple(const DevBox *boxes) {
     }
 }
 
-// VJP source records in sorted order, two float4 per slot: the slot's offset
-// (ox, oy, oz, cz) and its caller-order cotangent gathered to it (vx, vy, vz, 0),
-// so that a source is one 32-byte record.
 __global__ void __launch_bounds__(256) k_gather_cot(const DevBox *boxes, float4 *cot_sorted) {
-    const DevBox &B = boxes[blockIdx.y];
-    const int s = blockIdx.x * 256 + threadIdx.x;
-    if (s >= B.n) return;
-    const int i = B.order[s];
-    if (i < 0 || i >= B.n) return;
-    const float *v = B.cot + 3 * (int64_t)i;
-    cot_sorted[2 * (B.base + s)] = B.off[s];
-    cot_sorted[2 * (B.base + s) + 1] = make_float4(v[0], v[1], v[2], 0.0f);
+    gather_cot(boxes[blockIdx.y], cot_sorted, (int64_t)blockIdx.x * 256 + threadIdx.x);
 }
 
 // VJP per pair: with r = x_j - x_i (cell widths), g = F/r and h = g'(rho)/rho,
@@ -218,17 +208,11 @@ hipError_t accel_launch(const DevBox *d_boxes, int nbox, const ForcePlan &p, hip
     return hipGetLastError();
 }
 
-hipError_t gather_cot_launch(const DevBox *d_boxes, int nbox, const ForcePlan &p, hipStream_t s) {
-    if (p.max_n == 0) return hipSuccess;
-    dim3 grid((unsigned)((p.max_n + 255) / 256), (unsigned)nbox);
-    hipLaunchKernelGGL(k_gather_cot, grid, dim3(256), 0, s, d_boxes, p.cot_sorted);
-    return hipGetLastError();
-}
-
 hipError_t vjp_launch(const DevBox *d_boxes, int nbox, const ForcePlan &p, hipStream_t s) {
     if (p.max_n == 0) return hipSuccess;
     dim3 grid((unsigned)((p.max_n + 255) / 256), (unsigned)nbox);
-    hipError_t e = gather_cot_launch(d_boxes, nbox, p, s);
+    hipLaunchKernelGGL(k_gather_cot, grid, dim3(256), 0, s, d_boxes, p.cot_sorted);
+    hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (p.compensated)
         hipLaunchKernelGGL(k_vjp_simple<true>, grid, dim3(256), 0, s, d_boxes,

@@ -22,24 +22,30 @@ int fail(int code, const std::string &msg) {
 }
 
 // Descriptor bytes travel as a kernel argument (no host-to-device memcpy), so
-// every call is a pure sequence of kernel launches.
-constexpr int kChunkBytes = 2048;
+// every call is a pure sequence of kernel launches.  3840 bytes and the other
+// arguments fit the 4 KB that kernel arguments may take.
+constexpr int kChunkBytes = 3840;
 struct Chunk {
     unsigned char bytes[kChunkBytes];
 };
 
-__global__ void k_put_bytes(Chunk c, unsigned char *dst, int nbytes) {
+// The bytes to dst, and nzero words of zeros to zero.
+__global__ void __launch_bounds__(256)
+k_put_bytes(Chunk c, unsigned char *dst, int nbytes, uint32_t *zero, int nzero) {
     for (int i = threadIdx.x; i < nbytes; i += blockDim.x) dst[i] = c.bytes[i];
+    for (int i = threadIdx.x; i < nzero; i += blockDim.x) zero[i] = 0u;
 }
 
-hipError_t upload(const void *src, size_t nbytes, void *dst, hipStream_t s) {
+hipError_t upload(const void *src, size_t nbytes, void *dst, hipStream_t s,
+                  uint32_t *zero = nullptr, int nzero = 0) {
     const unsigned char *p = static_cast<const unsigned char *>(src);
     unsigned char *d = static_cast<unsigned char *>(dst);
     for (size_t o = 0; o < nbytes; o += kChunkBytes) {
         Chunk c;
         int m = (int)std::min<size_t>(kChunkBytes, nbytes - o);
         std::memcpy(c.bytes, p + o, (size_t)m);
-        hipLaunchKernelGGL(k_put_bytes, dim3(1), dim3(256), 0, s, c, d + o, m);
+        hipLaunchKernelGGL(k_put_bytes, dim3(1), dim3(256), 0, s, c, d + o, m, zero,
+                           o == 0 ? nzero : 0);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
@@ -198,8 +204,11 @@ int validate(int nbox, const nf_box *boxes, Layout &L, uint32_t flags = 0) {
     o = scratch0;
     L.cellinfo_off = o;
     o = align_up(o + 4 * (size_t)L.C, 256);
+    // zeroed together by the call's upload: bucket counts and cursors, queue
+    // counters (plan_zero_words)
     L.bucket_off = o;
-    o = align_up(o + 4 * 2 * (size_t)plan_buckets(), 256);
+    L.counter_off = o + 4 * (size_t)plan_buckets();
+    o = align_up(L.counter_off + 4 * (size_t)queue_words(), 256);
     L.totals_off = o;
     o = align_up(o + 16, 256);
     // dense items: at most max_dense (counted per box above); light: <= 1 per cell
@@ -208,8 +217,6 @@ int validate(int nbox, const nf_box *boxes, Layout &L, uint32_t flags = 0) {
     o = align_up(o + sizeof(Item) * (size_t)L.max_dense, 256);
     L.light_off = o;
     o = align_up(o + sizeof(Item) * (size_t)(L.C + 16), 256);
-    L.counter_off = o;
-    o = align_up(o + 4 * (size_t)queue_words(), 256);
     L.accel_end = o;
     L.cot_off = o;   // VJP source records: 32 bytes per particle
     o = align_up(o + 32 * (size_t)L.N, 256);
@@ -433,9 +440,6 @@ int nf_bin_particles(int nbox, const nf_box *boxes, void *ws, size_t ws_bytes, v
 }
 
 
-// noalloc: the workspace is the static `scratch` array of the current device
-// (ws and ws_bytes are ignored), and the force kernels run one after another
-// on the caller's stream (no library side streams or events).
 // The planner's tables inside the workspace.
 static TilePlan tile_plan(const Layout &L, char *w) {
     TilePlan tp;
@@ -443,7 +447,6 @@ static TilePlan tile_plan(const Layout &L, char *w) {
     tp.max_cells = L.max_ncell;
     tp.cellinfo = reinterpret_cast<uint32_t *>(w + L.cellinfo_off);
     tp.bucket_cnt = reinterpret_cast<uint32_t *>(w + L.bucket_off);
-    tp.bucket_off = tp.bucket_cnt + plan_buckets();
     tp.totals = reinterpret_cast<uint32_t *>(w + L.totals_off);
     tp.dense = reinterpret_cast<Item *>(w + L.dense_off);
     tp.light = reinterpret_cast<Item *>(w + L.light_off);
@@ -453,6 +456,11 @@ static TilePlan tile_plan(const Layout &L, char *w) {
     return tp;
 }
 
+static int plan_zero_words() { return plan_buckets() + queue_words(); }
+
+// noalloc: the workspace is the static `scratch` array of the current device
+// (ws and ws_bytes are ignored), and the force kernels run one after another
+// on the caller's stream (no library side streams or events).
 static int force_common(int nbox, const nf_box *boxes, double gm, uint32_t flags,
                         const float *const *cot, float *const *out, void *ws, size_t ws_bytes,
                         void *stream, bool vjp, bool noalloc = false) {
@@ -531,7 +539,10 @@ static int force_common(int nbox, const nf_box *boxes, double gm, uint32_t flags
     }
     hipStream_t s = static_cast<hipStream_t>(stream);
     DevBox *d_tab = reinterpret_cast<DevBox *>(w + L.table_off);
-    hipError_t e = upload(tab.data(), sizeof(DevBox) * tab.size(), d_tab, s);
+    const bool tiled = !(flags & NF_SIMPLE) && L.N > 0;
+    hipError_t e = upload(tab.data(), sizeof(DevBox) * tab.size(), d_tab, s,
+                          reinterpret_cast<uint32_t *>(w + L.bucket_off),
+                          tiled ? plan_zero_words() : 0);
     if (e != hipSuccess) return fail(NF_EHIP, std::string("upload: ") + hipGetErrorString(e));
     ForcePlan p;
     p.max_n = L.max_n;
@@ -539,12 +550,11 @@ static int force_common(int nbox, const nf_box *boxes, double gm, uint32_t flags
     p.compensated = (flags & NF_COMPENSATED) != 0;
     p.simple = (flags & NF_SIMPLE) != 0;
     p.cot_sorted = reinterpret_cast<float4 *>(w + L.cot_off);
-    if (p.simple || L.N == 0) {
+    if (!tiled) {
         e = vjp ? vjp_launch(d_tab, nbox, p, s) : accel_launch(d_tab, nbox, p, s);
     } else {
         const TilePlan tp = tile_plan(L, w);
-        e = vjp ? gather_cot_launch(d_tab, nbox, p, s) : hipSuccess;
-        if (e == hipSuccess) e = plan_launch(d_tab, nbox, tp, s);
+        e = plan_launch(d_tab, nbox, tp, vjp ? p.cot_sorted : nullptr, L.max_n, s);
         if (e == hipSuccess && use_f4) e = f4_plan_launch(d_tab, nbox, fp, s);
         if (e == hipSuccess)
             e = tile_launch(d_tab, vjp ? 1 : 0, p.compensated, tp, p.cot_sorted,
@@ -602,9 +612,10 @@ int nf_plan_items(int nbox, const nf_box *boxes, int32_t *items, int64_t max_ite
         for (int b = 0; b < nbox; ++b) fill_geometry(boxes[b], L, b, tab[b]);
         hipStream_t s = static_cast<hipStream_t>(stream);
         DevBox *d_tab = reinterpret_cast<DevBox *>(w + L.table_off);
-        hipError_t e = upload(tab.data(), sizeof(DevBox) * tab.size(), d_tab, s);
+        hipError_t e = upload(tab.data(), sizeof(DevBox) * tab.size(), d_tab, s,
+                              reinterpret_cast<uint32_t *>(w + L.bucket_off), plan_zero_words());
         const TilePlan tp = tile_plan(L, w);
-        if (e == hipSuccess) e = plan_launch(d_tab, nbox, tp, s);
+        if (e == hipSuccess) e = plan_launch(d_tab, nbox, tp, nullptr, 0, s);
         if (e == hipSuccess) e = plan_export_launch(tp, items, max_items, counts, s);
         if (e != hipSuccess) return fail(NF_EHIP, std::string("plan launch: ") + hipGetErrorString(e));
         g_last_error.clear();

@@ -99,16 +99,30 @@ __device__ __forceinline__ float4 ld_off4(const float4 *off, int64_t i) {
 
 // Element i of a float4 array through a global-address-space pointer.
 typedef float nf_v4f __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ void st_g4(float4 *base, uint64_t i, float x, float y, float z) {
+__device__ __forceinline__ void st_g4(float4 *base, uint64_t i, float x, float y, float z,
+                                      float w = 0.f) {
     __attribute__((address_space(1))) nf_v4f *p =
         (__attribute__((address_space(1))) nf_v4f *)base + i;
-    nf_v4f v = {x, y, z, 0.f};
+    nf_v4f v = {x, y, z, w};
     *p = v;
 }
 __device__ __forceinline__ nf_v4f ld_g4(const float4 *base, uint64_t i) {
     const __attribute__((address_space(1))) nf_v4f *p =
         (const __attribute__((address_space(1))) nf_v4f *)base + i;
     return *p;
+}
+
+// VJP source record of sorted slot s, two float4 per slot: the slot's offset
+// (ox, oy, oz, cz) and its caller-order cotangent gathered to it (vx, vy, vz, 0),
+// so that a source is one 32-byte record.
+__device__ __forceinline__ void gather_cot(const DevBox &B, float4 *cot_sorted, int64_t s) {
+    if (s >= B.n) return;
+    const int i = gp(B.order)[s];
+    if (i < 0 || i >= B.n) return;   // never taken for a consistent binning
+    const gptr<const float> v = gp(B.cot) + 3 * (int64_t)i;
+    const nf_v4f o = ld_g4(B.off, (uint64_t)s);
+    st_g4(cot_sorted, 2 * (uint64_t)(B.base + s), o.x, o.y, o.z, o.w);
+    st_g4(cot_sorted, 2 * (uint64_t)(B.base + s) + 1, v[0], v[1], v[2]);
 }
 
 // A symmetric pair item: chunk `chunk` of cell `cell` against every chunk of

@@ -56,8 +56,7 @@ struct TilePlan {
     int64_t TG = 0;              // cells over all boxes (planning is per cell)
     int64_t max_cells = 0;       // largest per-box cell count
     uint32_t *cellinfo = nullptr;     // [TG] item kind and cost bucket per cell
-    uint32_t *bucket_cnt = nullptr;   // [plan_buckets()] items per (kind, cost bucket)
-    uint32_t *bucket_off = nullptr;   // [plan_buckets()] first item of each bucket
+    uint32_t *bucket_cnt = nullptr;   // [plan_buckets()] items per (kind, bucket), fill cursors
     uint32_t *totals = nullptr;  // [3] dense, light and narrow item counts
     Item *dense = nullptr;       // dense items, heaviest first
     Item *light = nullptr;       // light items, then narrow items, each in spatial slabs
@@ -67,7 +66,9 @@ struct TilePlan {
 };
 int plan_buckets();
 int queue_words();
-hipError_t plan_launch(const DevBox *d_boxes, int nbox, const TilePlan &tp, hipStream_t s);
+// The work list; cot non-null: the VJP's source records of all particles too.
+hipError_t plan_launch(const DevBox *d_boxes, int nbox, const TilePlan &tp, float4 *cot,
+                       int64_t max_n, hipStream_t s);
 // The planned items as (box, cell, chunk, class) int32 quadruples, dense,
 // light then narrow, at most max_items of them, and the three class counts.
 hipError_t plan_export_launch(const TilePlan &tp, int32_t *items, int64_t max_items,
@@ -147,6 +148,5 @@ struct ForcePlan {
 
 hipError_t accel_launch(const DevBox *d_boxes, int nbox, const ForcePlan &p, hipStream_t s);
 hipError_t vjp_launch(const DevBox *d_boxes, int nbox, const ForcePlan &p, hipStream_t s);
-hipError_t gather_cot_launch(const DevBox *d_boxes, int nbox, const ForcePlan &p, hipStream_t s);
 
 }  // namespace nf

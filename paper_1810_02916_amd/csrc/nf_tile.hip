@@ -78,20 +78,14 @@ __device__ __forceinline__ int scan_lanes(int x) {
 
 // ------------------------------------------------------------------ planner
 
-// Sources in the 5x5x5 block of cell (cx, cy, cz): 25 row ranges of 5 cells.
-__device__ int block_sources(gptr<const int32_t> cs, int K, int cx, int cy, int cz) {
-    int s = 0;
-    for (int r = 0; r < kRows; ++r) {
-        const int rb = (wrapk(cx + r / 5 - 2, K) * K + wrapk(cy + r % 5 - 2, K)) * K;
-        const int lo = cz - 2, hi = cz + 2;
-        if (lo < 0)
-            s += (cs[rb + K] - cs[rb + lo + K]) + (cs[rb + hi + 1] - cs[rb]);
-        else if (hi >= K)
-            s += (cs[rb + K] - cs[rb + lo]) + (cs[rb + hi - K + 1] - cs[rb]);
-        else
-            s += cs[rb + hi + 1] - cs[rb + lo];
-    }
-    return s;
+// Sources of row r = (dx+2)*5 + (dy+2) of the 5x5x5 block of cell (cx, cy, cz).
+__device__ __forceinline__ int row_sources(gptr<const int32_t> cs, int K, int cx, int cy, int cz,
+                                           int r) {
+    const int rb = (wrapk(cx + r / 5 - 2, K) * K + wrapk(cy + r % 5 - 2, K)) * K;
+    const int lo = cz - 2, hi = cz + 2;
+    if (lo < 0) return (cs[rb + K] - cs[rb + lo + K]) + (cs[rb + hi + 1] - cs[rb]);
+    if (hi >= K) return (cs[rb + K] - cs[rb + lo]) + (cs[rb + hi - K + 1] - cs[rb]);
+    return cs[rb + hi + 1] - cs[rb + lo];
 }
 
 // Buckets, placed highest first: dense items by cost (quarter octaves of
@@ -120,34 +114,59 @@ __device__ __forceinline__ CellItems cell_items(int n, int dense_min, int narrow
     return CellItems{full + (rem >= dense_min ? 1 : 0), lk};
 }
 
+// Blocks [0, cell_blocks): the items of 256 cells of box blockIdx.y.  S ranks
+// dense items only, and few cells hold one: the block lists them and its
+// threads take their (cell, row) pairs (one thread per cell walking its 25
+// rows kept nearly every wave in that loop for a lane or two: 24 us for 64^3
+// cells).  The remaining blocks gather the VJP's source records (gather_cot),
+// which need nothing of the plan.
 __global__ void __launch_bounds__(256)
-k_plan_count(const DevBox *boxes, uint32_t *cellinfo, uint32_t *bucket_cnt) {
-    __shared__ uint32_t h[kKinds * kBuckets];
-    for (int t = threadIdx.x; t < kKinds * kBuckets; t += 256) h[t] = 0;
-    __syncthreads();
+k_plan_count(const DevBox *boxes, uint32_t *cellinfo, uint32_t *bucket_cnt, int cell_blocks,
+             float4 *cot_sorted) {
     const DevBox &B = boxes[blockIdx.y];
+    if ((int)blockIdx.x >= cell_blocks) {
+        gather_cot(B, cot_sorted, (int64_t)(blockIdx.x - cell_blocks) * 256 + threadIdx.x);
+        return;
+    }
+    __shared__ uint32_t h[kKinds * kBuckets];
+    __shared__ int dcell[256], dsum[256];
+    __shared__ int nd;
+    for (int t = threadIdx.x; t < kKinds * kBuckets; t += 256) h[t] = 0;
+    dsum[threadIdx.x] = 0;
+    if (threadIdx.x == 0) nd = 0;
+    __syncthreads();
     const int c = blockIdx.x * 256 + threadIdx.x;
+    const int K = B.K;
+    const gptr<const int32_t> cs = gp(B.cell_start);
+    CellItems it{0, 0};
+    int at = 0;
     if (c < B.ncell) {
-        const gptr<const int32_t> cs = gp(B.cell_start);
-        const int n = cs[c + 1] - cs[c];
+        it = cell_items(cs[c + 1] - cs[c], B.dense_min, B.narrow_max);
+        if (it.ndense) {
+            at = atomicAdd(&nd, 1);
+            dcell[at] = c;
+        }
+    }
+    __syncthreads();
+    for (int t = threadIdx.x; t < nd * kRows; t += 256) {
+        const int d = dcell[t / kRows];
+        atomicAdd(&dsum[t / kRows],
+                  row_sources(cs, K, d / (K * K), (d / K) % K, d % K, t % kRows));
+    }
+    __syncthreads();
+    if (c < B.ncell) {
         uint32_t info = 0;
-        if (n > 0) {
-            const CellItems it = cell_items(n, B.dense_min, B.narrow_max);
-            if (it.ndense) {   // S (the block's sources) ranks dense items only
-                const int K = B.K;
-                const float S = (float)block_sources(cs, K, c / (K * K), (c / K) % K, c % K);
-                const int b = cost_bucket(S);
-                atomicAdd(&h[b], (uint32_t)it.ndense);
-                info |= (uint32_t)(b + 1);
-            }
-            if (it.light) {
-                // light items run in spatial order (slabs of consecutive cells):
-                // neighbouring items share their staged sources in L2, and the
-                // dense kernel, running alongside, absorbs the tail
-                const int b = kBuckets - 1 - (int)((int64_t)c * kBuckets / B.ncell);
-                atomicAdd(&h[it.light * kBuckets + b], 1u);
-                info |= (uint32_t)(b + 1) << 16;
-            }
+        if (it.ndense) {
+            const int b = cost_bucket((float)dsum[at]);
+            atomicAdd(&h[b], (uint32_t)it.ndense);
+            info |= (uint32_t)(b + 1);
+        }
+        if (it.light) {
+            // light items run in spatial order (slabs of consecutive cells):
+            // neighbouring items share their sources in L2
+            const int b = kBuckets - 1 - (int)((int64_t)c * kBuckets / B.ncell);
+            atomicAdd(&h[it.light * kBuckets + b], 1u);
+            info |= (uint32_t)(b + 1) << 16;
         }
         cellinfo[B.cellbase + c] = info;
     }
@@ -156,31 +175,31 @@ k_plan_count(const DevBox *boxes, uint32_t *cellinfo, uint32_t *bucket_cnt) {
         if (h[t]) atomicAdd(&bucket_cnt[t], h[t]);
 }
 
-// Bucket offsets per kind, heaviest bucket first; totals[kind] = item count.
-__global__ void __launch_bounds__(kKinds * kBuckets)
-k_plan_buckets(uint32_t *bucket_cnt, uint32_t *bucket_off, uint32_t *totals) {
-    __shared__ uint32_t c[kKinds * kBuckets];
-    const int t = threadIdx.x;
-    const int kind = t / kBuckets, bk = t % kBuckets;
-    c[t] = bucket_cnt[t];
-    __syncthreads();
-    uint32_t off = 0;
-    for (int b = kBuckets - 1; b > bk; --b) off += c[kind * kBuckets + b];
-    bucket_off[t] = off;
-    bucket_cnt[t] = 0;   // reused as the fill cursor by k_plan_emit
-    if (bk == 0) totals[kind] = off + c[t];
-}
-
-// Items into their bucket ranges: each block reserves one range per non-empty
-// bucket with a global atomic and places its cells by LDS ranks.  The order
-// inside a bucket depends on timing; every item's result does not.  Narrow
-// items follow the light ones in the same array.
+// Items into their bucket ranges: each block adds up the bucket counts of all
+// blocks (highest bucket first), reserves one range per non-empty bucket with a
+// global atomic and places its cells by LDS ranks.  The order inside a bucket
+// depends on timing; every item's result does not.  Narrow items follow the
+// light ones in the same array.
 __global__ void __launch_bounds__(256)
 k_plan_emit(const DevBox *boxes, const uint32_t *__restrict__ cellinfo,
-            const uint32_t *__restrict__ bucket_off, const uint32_t *__restrict__ totals,
-            uint32_t *bucket_cur, Item *dense, Item *light) {
+            const uint32_t *__restrict__ bucket_cnt, uint32_t *bucket_cur, uint32_t *totals,
+            Item *dense, Item *light) {
     __shared__ uint32_t h[kKinds * kBuckets];
     __shared__ uint32_t base[kKinds * kBuckets];
+    __shared__ uint32_t tot[kKinds];
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    if (wave < kKinds) {   // one wave per kind, two buckets per lane
+        static_assert(kBuckets == 128 && kKinds < 4, "two buckets per lane");
+        const int b0 = wave * kBuckets + kBuckets - 1 - 2 * lane;
+        const int c0 = (int)bucket_cnt[b0], c1 = (int)bucket_cnt[b0 - 1];
+        const int x = scan_lanes<64>(c0 + c1);
+        base[b0] = (uint32_t)(x - c0 - c1);
+        base[b0 - 1] = (uint32_t)(x - c1);
+        if (lane == 63) {
+            tot[wave] = (uint32_t)x;
+            if (blockIdx.x == 0 && blockIdx.y == 0) totals[wave] = (uint32_t)x;
+        }
+    }
     for (int t = threadIdx.x; t < kKinds * kBuckets; t += 256) h[t] = 0;
     __syncthreads();
     const DevBox &B = boxes[blockIdx.y];
@@ -201,14 +220,14 @@ k_plan_emit(const DevBox *boxes, const uint32_t *__restrict__ cellinfo,
     }
     __syncthreads();
     for (int t = threadIdx.x; t < kKinds * kBuckets; t += 256)
-        if (h[t]) base[t] = bucket_off[t] + atomicAdd(&bucket_cur[t], h[t]);
+        if (h[t]) base[t] += atomicAdd(&bucket_cur[t], h[t]);
     __syncthreads();
     if (it.ndense) {
         const uint32_t at = base[bd] + rd;
         for (int k = 0; k < it.ndense; ++k) dense[at + k] = Item{(int)blockIdx.y, c, 1, k};
     }
     if (it.light) {
-        const uint32_t at = (it.light == 2 ? totals[1] : 0u) + base[it.light * kBuckets + bl] + rl;
+        const uint32_t at = (it.light == 2 ? tot[1] : 0u) + base[it.light * kBuckets + bl] + rl;
         light[at] = Item{(int)blockIdx.y, c, 1, n / kUnit};
     }
 }
@@ -1174,8 +1193,8 @@ hipError_t launch_force(const DevBox *d_boxes, const TilePlan &tp, const float4 
 
 }  // namespace
 
-int plan_buckets() { return kKinds * kBuckets; }
-// dense queue, light and narrow queues, then the pair kernel's queue
+// bucket counts, then their fill cursors
+int plan_buckets() { return 2 * kKinds * kBuckets; }
 // dense queues (one per XCD), light queues, narrow queues, the pair kernel's
 int queue_words() { return (kXcds + 2 * kQueues + 1) * kQueueStride; }
 
@@ -1211,25 +1230,24 @@ hipError_t plan_export_launch(const TilePlan &tp, int32_t *items, int64_t max_it
     return hipGetLastError();
 }
 
-hipError_t plan_launch(const DevBox *d_boxes, int nbox, const TilePlan &tp, hipStream_t s) {
-    hipError_t e;
-    dim3 grid((unsigned)((tp.max_cells + 255) / 256), (unsigned)nbox);
-    if ((e = fill_u32(tp.bucket_cnt, kKinds * kBuckets, 0u, s)) != hipSuccess) return e;
-    hipLaunchKernelGGL(k_plan_count, grid, dim3(256), 0, s, d_boxes, tp.cellinfo, tp.bucket_cnt);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    hipLaunchKernelGGL(k_plan_buckets, dim3(1), dim3(kKinds * kBuckets), 0, s, tp.bucket_cnt,
-                       tp.bucket_off, tp.totals);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    hipLaunchKernelGGL(k_plan_emit, grid, dim3(256), 0, s, d_boxes,
-                       (const uint32_t *)tp.cellinfo, (const uint32_t *)tp.bucket_off,
-                       (const uint32_t *)tp.totals, tp.bucket_cnt, tp.dense, tp.light);
+// The bucket counts, the fill cursors and the queue counters are zeroed by the
+// call's descriptor upload.
+hipError_t plan_launch(const DevBox *d_boxes, int nbox, const TilePlan &tp, float4 *cot,
+                       int64_t max_n, hipStream_t s) {
+    const unsigned cb = (unsigned)((tp.max_cells + 255) / 256);
+    const unsigned gb = cot ? (unsigned)((max_n + 255) / 256) : 0u;
+    hipLaunchKernelGGL(k_plan_count, dim3(cb + gb, (unsigned)nbox), dim3(256), 0, s, d_boxes,
+                       tp.cellinfo, tp.bucket_cnt, (int)cb, cot);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_plan_emit, dim3(cb, (unsigned)nbox), dim3(256), 0, s, d_boxes,
+                       (const uint32_t *)tp.cellinfo, (const uint32_t *)tp.bucket_cnt,
+                       tp.bucket_cnt + kKinds * kBuckets, tp.totals, tp.dense, tp.light);
     return hipGetLastError();
 }
 
 hipError_t tile_launch(const DevBox *d_boxes, int mode, bool compensated, const TilePlan &tp,
                        const float4 *cot, bool concurrent, hipStream_t s, const F4Plan *f4) {
-    hipError_t e = fill_u32(tp.counter, queue_words(), 0u, s);
-    if (e != hipSuccess) return e;
     if (mode == 0)
         return compensated ? launch_force<0, true>(d_boxes, tp, cot, concurrent, s, f4)
                            : launch_force<0, false>(d_boxes, tp, cot, concurrent, s, f4);
