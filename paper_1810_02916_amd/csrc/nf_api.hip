@@ -445,6 +445,7 @@ static TilePlan tile_plan(const Layout &L, char *w) {
     TilePlan tp;
     tp.TG = L.C;
     tp.max_cells = L.max_ncell;
+    tp.particles = L.N;
     tp.cellinfo = reinterpret_cast<uint32_t *>(w + L.cellinfo_off);
     tp.bucket_cnt = reinterpret_cast<uint32_t *>(w + L.bucket_off);
     tp.totals = reinterpret_cast<uint32_t *>(w + L.totals_off);

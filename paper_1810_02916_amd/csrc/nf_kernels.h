@@ -55,6 +55,7 @@ hipError_t f4_combine_launch(const DevBox *d_boxes, int nbox, const F4Plan &fp, 
 struct TilePlan {
     int64_t TG = 0;              // cells over all boxes (planning is per cell)
     int64_t max_cells = 0;       // largest per-box cell count
+    int64_t particles = 0;       // particles over all boxes
     uint32_t *cellinfo = nullptr;     // [TG] item kind and cost bucket per cell
     uint32_t *bucket_cnt = nullptr;   // [plan_buckets()] items per (kind, bucket), fill cursors
     uint32_t *totals = nullptr;  // [3] dense, light and narrow item counts

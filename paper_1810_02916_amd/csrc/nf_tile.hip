@@ -708,6 +708,290 @@ k_dense(const DevBox *__restrict__ boxes, const Item *__restrict__ items,
     }
 }
 
+// ------------------------------------------------------------------ dense path, few items
+
+// A dense item by a whole workgroup, for calls with too few dense items to fill
+// the card: k_dense walks an item's sources on one wave, which alone on its
+// SIMD issues an operation every 5-7 clocks, so the call lasts as long as its
+// heaviest item (13 operations times up to thousands of sources).  A sink's sum
+// has to run through its sources in order, but only its last operation does:
+// kProducers waves compute the pairs' factors f and vectors e (F = f e: e = r,
+// or W r + u for the VJP) of groups of four sources, 64 sinks in the lanes as in
+// k_dense, and leave them in LDS; three consumer waves, one per component, add
+// them in order, each pair one fused multiply-add with the operands, the order
+// and the compensated folds of k_dense, so the sums are the same bit for bit.
+// Producers work one round of kProducers groups ahead of the consumers, in two
+// buffers, with one barrier per round.  LDS traffic (10 KB per 256 pairs) makes
+// a pair dearer than k_dense's once the card is full: see kWideMaxAccel.
+constexpr int kProducers = 5;
+constexpr int kWideThreads = 64 * (kProducers + 3);
+
+// The source cells of an item in order (c = 25 (dx+2) + 5 (dy+2) + dz+2), cut
+// into groups of at most four sources of one cell, and of one partial sum in
+// the compensated mode: lane l holds cells l and l + 64.
+struct CellGroups {
+    int beg[2], cnt[2], end[2];   // first slot, sources, groups up to and with the cell
+};
+
+template <bool COMP>
+__device__ __forceinline__ int groups_of(int n, int flush, int gpb) {
+    if constexpr (!COMP) return (n + 3) >> 2;
+    const int full = n / flush;
+    return full * gpb + ((n - full * flush + 3) >> 2);
+}
+
+// One group: its sources [j, j + count), its cell's direction, and whether it
+// ends a partial sum.
+struct Group {
+    int j, count, c;
+    bool ends;
+};
+template <bool COMP>
+__device__ __forceinline__ Group group_of(const CellGroups &G, int k, int flush, int gpb,
+                                          uint32_t gpb_inv) {
+    Group g;
+    const int c = (int)__popcll(__ballot(G.end[0] <= k)) + (int)__popcll(__ballot(G.end[1] <= k));
+    const int l = c & 63;
+    int beg, cnt, first;
+    if (c < 64) {
+        beg = __builtin_amdgcn_readlane(G.beg[0], l);
+        cnt = __builtin_amdgcn_readlane(G.cnt[0], l);
+        first = __builtin_amdgcn_readlane(G.end[0], l);
+    } else {
+        beg = __builtin_amdgcn_readlane(G.beg[1], l);
+        cnt = __builtin_amdgcn_readlane(G.cnt[1], l);
+        first = __builtin_amdgcn_readlane(G.end[1], l);
+    }
+    first -= groups_of<COMP>(cnt, flush, gpb);
+    const int i = k - first;
+    int from = 0, at = 4 * i, upto = cnt;
+    if constexpr (COMP) {
+        // i / gpb: i < 2^25 (a cell's groups), exact for gpb_inv = ceil(2^32 / gpb)
+        // up to i gpb < 2^32
+        const int b = gpb == 1 ? i : (int)__umulhi((uint32_t)i, gpb_inv);
+        from = b * flush;
+        at = from + 4 * (i - b * gpb);
+        upto = min(cnt, from + flush);
+    }
+    g.j = beg + at;
+    g.count = min(4, upto - at);
+    g.c = c;
+    g.ends = at + 4 >= upto;
+    return g;
+}
+
+// Four records from slot j on; past the array's end (the last cell's last
+// group) each is read by itself, the last valid slot again.
+template <int MODE>
+__device__ __forceinline__ Rec<4 * (MODE == 0 ? 4 : 8)> load_group(cfloat *src, int j, int n) {
+    constexpr int W = MODE == 0 ? 4 : 8;
+    if (j + 4 <= n) return load_rec<4 * W>(src + (int64_t)W * j);
+    Rec<4 * W> r;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const Rec<W> x = load_rec<W>(src + (int64_t)W * min(j + u, n - 1));
+#pragma unroll
+        for (int i = 0; i < W; ++i) r.w[W * u + i] = x.w[i];
+    }
+    return r;
+}
+
+// f and e of four pairs: the terms of pair_accelN and pair_vjp_sum without their
+// last operation.
+template <int MODE, bool SPLINE>
+__device__ __forceinline__ void pair_terms(const Sep<MODE, 4> &d, const Coef &k, float (&f)[4],
+                                           float (&ex)[4], float (&ey)[4], float (&ez)[4]) {
+    float r2[4], q[4], W[4], rdu[4];
+    bool in = false;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        r2[u] = __builtin_fmaf(d.x[u], d.x[u], k.floor);
+        r2[u] = __builtin_fmaf(d.y[u], d.y[u], r2[u]);
+        r2[u] = __builtin_fmaf(d.z[u], d.z[u], r2[u]);
+        q[u] = __builtin_amdgcn_rsqf(r2[u]);
+        if constexpr (MODE == 0) {
+            f[u] = q[u] * q[u] * q[u];
+        } else {
+            rdu[u] = d.x[u] * d.u[u];
+            rdu[u] = __builtin_fmaf(d.y[u], d.v[u], rdu[u]);
+            rdu[u] = __builtin_fmaf(d.z[u], d.w[u], rdu[u]);
+            const float q2 = q[u] * q[u];
+            f[u] = q2 * q[u];
+            W[u] = (-3.0f * q2) * rdu[u];
+        }
+        if constexpr (SPLINE) in |= r2[u] < k.eps2;
+    }
+    if constexpr (SPLINE) {
+        if (__any(in)) {
+            asm volatile("");
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const float rho = r2[u] * q[u];
+                const float g = __builtin_fmaf(__builtin_fmaf(k.cC, rho, k.cB), rho, k.cA);
+                const bool inside = r2[u] < k.eps2;
+                if constexpr (MODE == 0) {
+                    f[u] = inside ? fminf(g, f[u]) : f[u];
+                } else {
+                    const float h = __builtin_fmaf(k.cB, q[u], k.cC2);
+                    f[u] = inside ? g : f[u];
+                    W[u] = inside ? (h * rdu[u]) / g : W[u];
+                }
+            }
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        if constexpr (MODE == 0) {
+            ex[u] = d.x[u];
+            ey[u] = d.y[u];
+            ez[u] = d.z[u];
+        } else {
+            ex[u] = __builtin_fmaf(W[u], d.x[u], d.u[u]);
+            ey[u] = __builtin_fmaf(W[u], d.y[u], d.v[u]);
+            ez[u] = __builtin_fmaf(W[u], d.z[u], d.w[u]);
+        }
+    }
+}
+
+template <int MODE, bool COMP>
+__global__ void __launch_bounds__(kWideThreads)
+k_dense_wide(const DevBox *__restrict__ boxes, const Item *__restrict__ items,
+             const uint32_t *__restrict__ totals, uint32_t *counter,
+             const float4 *__restrict__ cot_sorted) {
+    // per buffer and group: f, then the three components of e, four pairs a lane
+    __shared__ float4 terms[2][kProducers][4][64];
+    __shared__ int ends[2][kProducers];
+    __shared__ int s_item;
+    const int lane = threadIdx.x & 63, wave = uni(threadIdx.x >> 6);
+    const int nitems = (int)totals[0];
+    const int x = (int)(blockIdx.x % kXcds);   // one queue per XCD, as k_dense
+    uint32_t *dq = counter + kQueueStride * x;
+    for (;;) {
+        if (threadIdx.x == 0) {
+            const int t = (int)__hip_atomic_fetch_add(gp(dq), 1u, __ATOMIC_RELAXED,
+                                                      __HIP_MEMORY_SCOPE_AGENT);
+            s_item = t * kXcds + x;   // few items: dealt singly
+        }
+        __syncthreads();
+        const int itx = uni(s_item);
+        __syncthreads();
+        if (itx >= nitems) break;
+        const gptr<const Item> ip = gp(items) + itx;
+        const Item I{ip->box, ip->cell0, ip->m, ip->chunk};
+        const DevBox &B = boxes[I.box];
+        const int K = B.K;
+        const int cx = I.cell0 / (K * K), cy = (I.cell0 / K) % K, z = I.cell0 % K;
+        const gptr<const int32_t> cs = gp(B.cell_start);
+        const int s0 = uni(cs[I.cell0] + kUnit * I.chunk);
+        const int g = uni(min(cs[I.cell0 + 1] - s0, kUnit));
+        const bool active = lane < g;   // lanes past the g sinks repeat sink 0
+        const int slot = s0 + (active ? lane : 0);
+        const int flush = uni(B.flush), gpb = (flush + 3) >> 2;
+        const uint32_t gpb_inv = 0xffffffffu / (uint32_t)gpb + 1u;   // unused for gpb = 1
+        CellGroups G;
+        {
+            int ng[2];
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const int c = min(lane + 64 * h, 124), r = c / 5;
+                const int cell = (wrapk(cx + r / 5 - 2, K) * K + wrapk(cy + r % 5 - 2, K)) * K +
+                                 wrapk(z + c % 5 - 2, K);
+                const int b = max(cs[cell], 0), e = min(cs[cell + 1], B.n);
+                G.beg[h] = b;
+                G.cnt[h] = lane + 64 * h < 125 ? max(e - b, 0) : 0;
+                ng[h] = groups_of<COMP>(G.cnt[h], flush, gpb);
+            }
+            G.end[0] = scan_lanes<64>(ng[0]);
+            G.end[1] = scan_lanes<64>(ng[1]) + __builtin_amdgcn_readlane(G.end[0], 63);
+        }
+        const int ngroups = __builtin_amdgcn_readlane(G.end[1], 63);
+        const int rounds = (ngroups + kProducers - 1) / kProducers;
+        if (wave < kProducers) {
+            const float4 oi = ld_global4((gfloat *)B.off, slot);
+            float4 vi = make_float4(0.f, 0.f, 0.f, 0.f);
+            if constexpr (MODE == 1)
+                vi = ld_global4((gfloat *)cot_sorted, 2 * (B.base + slot) + 1);
+            Coef k{B.cA, B.cB, B.cC, 2.0f * B.cC, B.eps * B.eps, B.r2floor};
+            in_vector(k.floor);
+            const bool fast = B.outer_newton != 0, plummer = B.plummer != 0;
+            cfloat *src =
+                MODE == 0 ? (cfloat *)B.off : (cfloat *)(cot_sorted + 2 * B.base);
+            int kg = wave;
+            Group gr = group_of<COMP>(G, min(kg, ngroups - 1), flush, gpb, gpb_inv);
+            auto rec = load_group<MODE>(src, gr.j, B.n);
+            for (int t = 0; t <= rounds; ++t) {
+                if (kg < ngroups) {
+                    const int c = gr.c, r = c / 5;
+                    const int dx = r / 5 - 2, dy = r % 5 - 2, dz = c % 5 - 2;
+                    const float xs = oi.x - (float)dx, ys = oi.y - (float)dy,
+                                zs = oi.z - (float)dz;
+                    const bool inner = dx >= -1 && dx <= 1 && dy >= -1 && dy <= 1 && dz >= -1 &&
+                                       dz <= 1;
+                    const Sep<MODE, 4> d = separations<MODE, 4>(rec, xs, ys, zs, vi);
+                    const int count = gr.count;
+                    const bool e = gr.ends;
+                    kg += kProducers;
+                    gr = group_of<COMP>(G, min(kg, ngroups - 1), flush, gpb, gpb_inv);
+                    __builtin_amdgcn_sched_barrier(0);
+                    rec = load_group<MODE>(src, gr.j, B.n);
+                    __builtin_amdgcn_sched_barrier(0);
+                    float f[4], ex[4], ey[4], ez[4];
+                    if (!plummer && (!fast || inner))
+                        pair_terms<MODE, true>(d, k, f, ex, ey, ez);
+                    else
+                        pair_terms<MODE, false>(d, k, f, ex, ey, ez);
+                    // past the group's sources: 0 times 0 (a finite e would do
+                    // for the sum, but another cell's cotangent may not be)
+#pragma unroll
+                    for (int u = 1; u < 4; ++u)
+                        if (u >= count) f[u] = ex[u] = ey[u] = ez[u] = 0.f;
+                    float4(*o)[64] = terms[t & 1][wave];
+                    o[0][lane] = make_float4(f[0], f[1], f[2], f[3]);
+                    o[1][lane] = make_float4(ex[0], ex[1], ex[2], ex[3]);
+                    o[2][lane] = make_float4(ey[0], ey[1], ey[2], ey[3]);
+                    o[3][lane] = make_float4(ez[0], ez[1], ez[2], ez[3]);
+                    if (lane == 0) ends[t & 1][wave] = e ? 1 : 0;
+                }
+                __syncthreads();
+            }
+        } else {
+            const int comp = wave - kProducers;
+            const int dst = gp(B.order)[slot];
+            float p = 0.f, sum = 0.f, low = 0.f;
+            for (int t = 0; t <= rounds; ++t) {
+                if (t > 0) {
+                    const int buf = (t - 1) & 1, m = min(kProducers, ngroups - (t - 1) * kProducers);
+                    const int last = COMP ? ends[buf][lane < kProducers ? lane : 0] : 0;
+                    float4 f[kProducers], e[kProducers];
+#pragma unroll
+                    for (int i = 0; i < kProducers; ++i) {
+                        f[i] = terms[buf][i][0][lane];
+                        e[i] = terms[buf][i][1 + comp][lane];
+                    }
+#pragma unroll
+                    for (int i = 0; i < kProducers; ++i) {
+                        if (i < m) {
+                            p = __builtin_fmaf(f[i].x, e[i].x, p);
+                            p = __builtin_fmaf(f[i].y, e[i].y, p);
+                            p = __builtin_fmaf(f[i].z, e[i].z, p);
+                            p = __builtin_fmaf(f[i].w, e[i].w, p);
+                            if constexpr (COMP) {
+                                if (__builtin_amdgcn_readlane(last, i)) {
+                                    kahan(sum, low, p);
+                                    p = 0.f;
+                                }
+                            }
+                        }
+                    }
+                }
+                __syncthreads();
+            }
+            if (active && dst >= 0 && dst < B.n)
+                gp(B.out)[3 * (int64_t)dst + comp] = (COMP ? sum - low : p) * B.scale;
+        }
+    }
+}
+
 // ------------------------------------------------------------------ light path
 
 // Pieces of the staged union: per row r = (dx+2)*5 + (dy+2) up to four
@@ -1241,9 +1525,28 @@ hipError_t launch_narrow(const DevBox *d_boxes, const TilePlan &tp, const float4
     }
 }
 
+// k_dense_wide takes the dense items of calls of at most this many particles
+// (over all boxes).  Whole force calls with k_dense / k_dense_wide, clustered
+// boxes, us: 20k particles plain 139 / 96, VJP 204 / 116; 50k 161 / 120, 267 /
+// 156; 131k 247 / 238 (compensated 263 / 270), 429 / 303; 262k 326 / 393, 632 /
+// 506; 524k 492 / 732, 885 / 959.
+constexpr int64_t kWideMaxAccel = 100000, kWideMaxVjp = 300000;
+
 template <int MODE, bool COMP>
-hipError_t launch_dense(const DevBox *d_boxes, const TilePlan &tp, const float4 *cot,
+hipError_t launch_dense_wide(const DevBox *d_boxes, const TilePlan &tp, const float4 *cot,
+                             hipStream_t s) {
+    static const int grid =
+        (persistent_grid(k_dense_wide<MODE, COMP>, kWideThreads) + kXcds - 1) / kXcds * kXcds;
+    hipLaunchKernelGGL((k_dense_wide<MODE, COMP>), dim3(grid), dim3(kWideThreads), 0, s, d_boxes,
+                       (const Item *)tp.dense, (const uint32_t *)tp.totals, tp.counter, cot);
+    return hipGetLastError();
+}
+
+template <int MODE, bool COMP>
+hipError_t launch_dense(const DevBox *d_boxes, const TilePlan &tp, const float4 *cot, bool f4,
                         hipStream_t s) {
+    if (!f4 && tp.particles <= (MODE == 0 ? kWideMaxAccel : kWideMaxVjp))
+        return launch_dense_wide<MODE, COMP>(d_boxes, tp, cot, s);
     // every XCD queue needs at least one workgroup: a multiple of kXcds
     static const int grid =
         (persistent_grid(k_dense<MODE, COMP>, kUnit) + kXcds - 1) / kXcds * kXcds;
@@ -1259,7 +1562,7 @@ hipError_t launch_force(const DevBox *d_boxes, const TilePlan &tp, const float4 
     if (!concurrent) {   // the kernels in turn on the caller's stream
         if ((e = launch_light<MODE, COMP>(d_boxes, tp, cot, s)) != hipSuccess) return e;
         if ((e = launch_narrow<MODE, COMP>(d_boxes, tp, cot, s)) != hipSuccess) return e;
-        if ((e = launch_dense<MODE, COMP>(d_boxes, tp, cot, s)) != hipSuccess) return e;
+        if ((e = launch_dense<MODE, COMP>(d_boxes, tp, cot, f4 != nullptr, s)) != hipSuccess) return e;
         if (f4 && (e = f4_ring_launch(d_boxes, *f4, COMP, s)) != hipSuccess) return e;
         return hipSuccess;
     }
@@ -1273,7 +1576,7 @@ hipError_t launch_force(const DevBox *d_boxes, const TilePlan &tp, const float4 
     if ((e = hipEventRecord(ss.join[0], ss.s[0])) != hipSuccess) return e;
     if ((e = launch_narrow<MODE, COMP>(d_boxes, tp, cot, ss.s[1])) != hipSuccess) return e;
     if ((e = hipEventRecord(ss.join[1], ss.s[1])) != hipSuccess) return e;
-    if ((e = launch_dense<MODE, COMP>(d_boxes, tp, cot, s)) != hipSuccess) return e;
+    if ((e = launch_dense<MODE, COMP>(d_boxes, tp, cot, f4 != nullptr, s)) != hipSuccess) return e;
     if (f4 && (e = f4_ring_launch(d_boxes, *f4, COMP, s)) != hipSuccess) return e;
     for (int k = 0; k < 2; ++k)
         if ((e = hipStreamWaitEvent(s, ss.join[k], 0)) != hipSuccess) return e;

@@ -340,6 +340,32 @@ def test_tile_item_classes_by_cell_count(dense_min):
                      tag=f"class {k} vjp comp={comp}")
 
 
+@pytest.mark.parametrize("law", ["spline", "wide spline", "plummer"])
+def test_dense_items_of_small_and_large_calls_bitwise(law):
+    """Dense items of a small call are summed by a whole workgroup in groups of
+    up to four sources, those of a large call by one wave: the same bits for
+    cells of 0..5 sources, remainders of 1..4, empty groups, the last cell at
+    the end of the array, and partial sums that are no multiple of four."""
+    K, L = 6, 1.0
+    pos = _gpu(_box_with_counts(K, L, [2, 0, 3, 65, 4, 1, 5, 33, 0, 66, 64, 7, 129], seed=21))
+    far = _gpu(uniform_box(310000, L, seed=22))
+    eps = (1.7 if law == "wide spline" else 0.2) * L / K
+    plummer = law == "plummer"
+    v = torch.from_numpy(gaussian_cotangent(len(pos), 23).astype(np.float32)).to(DEV)
+    for flush in (0, 1, 5, 33):
+        tiles = nfp.Tiles(dense_min=2, flush=flush)
+        one = nfp.bin_particles(pos, K, L, eps)
+        two = nfp.bin_particles_batched([pos, far], [K, 32], [L, L], [eps, 0.01])
+        one.set_tiles(tiles)
+        two.set_tiles(tiles)
+        for comp in (False, True):
+            print(f"[dense] {law} flush {flush} comp {comp}", flush=True)
+            kw = dict(compensated=comp, plummer=plummer)
+            assert torch.equal(nfp.accel(one, 1.0, **kw), nfp.accel(two, 1.0, **kw)[0])
+            assert torch.equal(nfp.accel_vjp(one, v, 1.0, **kw),
+                               nfp.accel_vjp(two, [v, torch.ones_like(far).float()], 1.0, **kw)[0])
+
+
 def test_tile_all_items_narrow():
     """A sparse box (at most 11 particles per cell): every item is narrow and
     the dense and light kernels find empty queues."""
