@@ -446,6 +446,8 @@ static TilePlan tile_plan(const Layout &L, char *w) {
     tp.TG = L.C;
     tp.max_cells = L.max_ncell;
     tp.particles = L.N;
+    tp.max_dense = L.max_dense;
+    tp.max_light = std::max<int64_t>(1, std::min(L.C, L.N));
     tp.cellinfo = reinterpret_cast<uint32_t *>(w + L.cellinfo_off);
     tp.bucket_cnt = reinterpret_cast<uint32_t *>(w + L.bucket_off);
     tp.totals = reinterpret_cast<uint32_t *>(w + L.totals_off);

@@ -56,6 +56,8 @@ struct TilePlan {
     int64_t TG = 0;              // cells over all boxes (planning is per cell)
     int64_t max_cells = 0;       // largest per-box cell count
     int64_t particles = 0;       // particles over all boxes
+    int64_t max_dense = 0;       // bound on the dense items
+    int64_t max_light = 0;       // bound on the light items, and on the narrow ones
     uint32_t *cellinfo = nullptr;     // [TG] item kind and cost bucket per cell
     uint32_t *bucket_cnt = nullptr;   // [plan_buckets()] items per (kind, bucket), fill cursors
     uint32_t *totals = nullptr;  // [3] dense, light and narrow item counts

@@ -47,8 +47,8 @@ namespace {
 constexpr int kUnit = 64;            // sinks per wave
 constexpr int kQueues = 32;          // light-item queues (a multiple of the 8 XCDs)
 constexpr int kXcds = 8;             // workgroups are dealt to the XCDs round-robin by id
-constexpr int kXcdBlock = 256;       // consecutive light items kept on one XCD
-constexpr int kDenseBlock = 16;      // consecutive dense items kept on one XCD
+constexpr int kXcdBlock = 256;       // consecutive light items kept on one XCD, at most
+constexpr int kDenseBlock = 16;      // consecutive dense items kept on one XCD, at most
 constexpr int kQueueStride = 32;     // words between queue counters (own 128-byte line)
 constexpr int kLightWaves = 4;       // waves sharing one light item
 constexpr int kLightThreads = 64 * kLightWaves;
@@ -57,6 +57,19 @@ constexpr int kRows = 25;            // (dx, dy) rows of the 5x5x5 block
 
 __device__ __forceinline__ int wrapk(int c, int K) { return c < 0 ? c + K : (c >= K ? c - K : c); }
 __device__ __forceinline__ int uni(int x) { return __builtin_amdgcn_readfirstlane(x); }
+
+// log2 of the consecutive items that stay on one XCD: `most`, or less so that
+// every XCD gets at least eight blocks (blocks of 256 left 463 light items on
+// two of the eight XCDs).
+__device__ __forceinline__ int xcd_block_log2(int nitems, int most) {
+    int b = 31 - __builtin_clz(most);
+    while (b > 0 && nitems < 8 * kXcds << b) --b;
+    return b;
+}
+// Item number of claim t of XCD x's queue: XCD x takes the blocks x, x + 8, ...
+__device__ __forceinline__ int xcd_item(int t, int x, int b) {
+    return ((((t >> b) * kXcds) + x) << b) + (t & ((1 << b) - 1));
+}
 
 // Inclusive prefix sums over the lanes of a wave (all 64 lanes active): a
 // Kogge-Stone scan inside each row of 16 lanes by DPP row shifts (one
@@ -606,17 +619,18 @@ k_dense(const DevBox *__restrict__ boxes, const Item *__restrict__ items,
     const int lane = threadIdx.x;
     const int nitems = (int)totals[0];
     // one queue per XCD (workgroup w runs on XCD w % 8): XCD x takes the
-    // blocks of kDenseBlock consecutive items c = x, x + 8, ... in order, so
+    // blocks of up to kDenseBlock consecutive items c = x, x + 8, ... in order, so
     // the chunks of one cell, which share every source, meet in one L2, and
     // the heaviest items still come first everywhere (the map is one-to-one
     // and increasing, so only the locality depends on the placement)
     const int x = (int)(blockIdx.x % kXcds);
+    const int xb = xcd_block_log2(nitems, kDenseBlock);
     uint32_t *dq = counter + kQueueStride * x;
     for (;;) {
         if (lane == 0) {
             const int t = (int)__hip_atomic_fetch_add(gp(dq), 1u, __ATOMIC_RELAXED,
                                                       __HIP_MEMORY_SCOPE_AGENT);
-            s_item = ((t / kDenseBlock) * kXcds + x) * kDenseBlock + t % kDenseBlock;
+            s_item = xcd_item(t, x, xb);
         }
         __syncthreads();
         const int itx = uni(s_item);
@@ -1125,7 +1139,7 @@ k_light(const DevBox *__restrict__ boxes, const Item *__restrict__ all_items,
     // kQueues interleaved queues: workgroup w draws from queue q = w % kQueues
     // (a single counter would cap the item rate at what one address sustains
     // for atomics).  The workgroups of queue q run on XCD q % 8, and the
-    // queues of one XCD share blocks of kXcdBlock consecutive items (items
+    // queues of one XCD share blocks of up to kXcdBlock consecutive items (items
     // are in spatial order, so neighbours share their sources in that XCD's
     // L2): XCD x takes the blocks c = x, x + 8, ..., its four queues taking
     // its items in turn.  (q, k) -> item is one-to-one and increasing in k,
@@ -1133,9 +1147,10 @@ k_light(const DevBox *__restrict__ boxes, const Item *__restrict__ all_items,
     // only the L2 locality does.
     const int q = (int)(blockIdx.x % kQueues);
     uint32_t *qc = counter + kQueueStride * q;
-    auto queue_item = [q](int kth) {
-        const int t = kth * (kQueues / kXcds) + q / kXcds;   // the XCD's t-th item
-        return ((t / kXcdBlock) * kXcds + q % kXcds) * kXcdBlock + t % kXcdBlock;
+    const int xb = xcd_block_log2(nitems, kXcdBlock);
+    auto queue_item = [q, xb](int kth) {
+        // the XCD's t-th item
+        return xcd_item(kth * (kQueues / kXcds) + q / kXcds, q % kXcds, xb);
     };
     if (lane == 0) {
         const int first = queue_item((int)__hip_atomic_fetch_add(gp(qc), 1u, __ATOMIC_RELAXED,
@@ -1441,6 +1456,14 @@ int persistent_grid(Kern kern, int threads) {
     return std::max(1, ncu) * std::max(1, per);
 }
 
+// A persistent grid of `most` workgroups, or fewer where the call cannot have
+// that many items (every workgroup ends with one claim that finds its queue
+// empty, and one counter takes about 87 M claims a second: 7168 idle workgroups
+// of k_dense on eight counters took 16 us).  A multiple of the queues.
+int grid_for(int most, int64_t items, int queues) {
+    return (int)std::min<int64_t>(most, (items + queues - 1) / queues * queues);
+}
+
 // The dense, light and narrow kernels of one call run concurrently: the
 // light and narrow kernels go to two library streams of the same device
 // (default priority), forked from and joined back to the caller's stream with
@@ -1485,8 +1508,9 @@ hipError_t side_stream(SideStream &out) {   // caller holds g_side_mu
 template <int MODE, bool COMP, int CAP, int NT>
 hipError_t launch_light_inst(const DevBox *d_boxes, const TilePlan &tp, const float4 *cot,
                              uint32_t *counter, int cls, hipStream_t s) {
-    static const int grid =
+    static const int most =
         (persistent_grid(k_light<MODE, COMP, CAP, NT>, NT) + kQueues - 1) / kQueues * kQueues;
+    const int grid = grid_for(most, tp.max_light, kQueues);
     hipLaunchKernelGGL((k_light<MODE, COMP, CAP, NT>), dim3(grid), dim3(NT), 0, s, d_boxes,
                        (const Item *)tp.light, (const uint32_t *)tp.totals, counter, cot, cls);
     return hipGetLastError();
@@ -1535,8 +1559,9 @@ constexpr int64_t kWideMaxAccel = 100000, kWideMaxVjp = 300000;
 template <int MODE, bool COMP>
 hipError_t launch_dense_wide(const DevBox *d_boxes, const TilePlan &tp, const float4 *cot,
                              hipStream_t s) {
-    static const int grid =
+    static const int most =
         (persistent_grid(k_dense_wide<MODE, COMP>, kWideThreads) + kXcds - 1) / kXcds * kXcds;
+    const int grid = grid_for(most, tp.max_dense, kXcds);
     hipLaunchKernelGGL((k_dense_wide<MODE, COMP>), dim3(grid), dim3(kWideThreads), 0, s, d_boxes,
                        (const Item *)tp.dense, (const uint32_t *)tp.totals, tp.counter, cot);
     return hipGetLastError();
@@ -1548,8 +1573,9 @@ hipError_t launch_dense(const DevBox *d_boxes, const TilePlan &tp, const float4 
     if (!f4 && tp.particles <= (MODE == 0 ? kWideMaxAccel : kWideMaxVjp))
         return launch_dense_wide<MODE, COMP>(d_boxes, tp, cot, s);
     // every XCD queue needs at least one workgroup: a multiple of kXcds
-    static const int grid =
+    static const int most =
         (persistent_grid(k_dense<MODE, COMP>, kUnit) + kXcds - 1) / kXcds * kXcds;
+    const int grid = grid_for(most, tp.max_dense, kXcds);
     hipLaunchKernelGGL((k_dense<MODE, COMP>), dim3(grid), dim3(kUnit), 0, s, d_boxes,
                        (const Item *)tp.dense, (const uint32_t *)tp.totals, tp.counter, cot);
     return hipGetLastError();
