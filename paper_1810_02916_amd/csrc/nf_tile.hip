@@ -729,22 +729,29 @@ k_dense(const DevBox *__restrict__ boxes, const Item *__restrict__ items,
 // SIMD issues an operation every 5-7 clocks, so the call lasts as long as its
 // heaviest item (13 operations times up to thousands of sources).  A sink's sum
 // has to run through its sources in order, but only its last operation does:
-// kProducers waves compute the pairs' factors f and vectors e (F = f e: e = r,
+// P waves compute the pairs' factors f and vectors e (F = f e: e = r,
 // or W r + u for the VJP) of groups of four sources, 64 sinks in the lanes as in
 // k_dense, and leave them in LDS; three consumer waves, one per component, add
 // them in order, each pair one fused multiply-add with the operands, the order
 // and the compensated folds of k_dense, so the sums are the same bit for bit.
-// Producers work one round of kProducers groups ahead of the consumers, in two
+// Producers work one round of P groups ahead of the consumers, in two
 // buffers, with one barrier per round.  LDS traffic (10 KB per 256 pairs) makes
-// a pair dearer than k_dense's once the card is full: see kWideMaxAccel.
-constexpr int kProducers = 5;
-constexpr int kWideThreads = 64 * (kProducers + 3);
+// a pair dearer than k_dense's once the card is full: see kWideMaxAccel.  P
+// producers: k_dense_wide five (three workgroups a CU), k_small thirteen.
+template <int P>
+struct WideSmem {
+    float4 terms[2][P][4][64];   // per buffer and group: f, then the components of e,
+                                 // four pairs a lane
+    int ends[2][P];
+    int item;
+};
 
 // The source cells of an item in order (c = 25 (dx+2) + 5 (dy+2) + dz+2), cut
 // into groups of at most four sources of one cell, and of one partial sum in
 // the compensated mode: lane l holds cells l and l + 64.
 struct CellGroups {
-    int beg[2], cnt[2], end[2];   // first slot, sources, groups up to and with the cell
+    int beg[2], cnt[2];     // first slot, sources
+    int first[2], end[2];   // groups before the cell, and with it
 };
 
 template <bool COMP>
@@ -770,13 +777,12 @@ __device__ __forceinline__ Group group_of(const CellGroups &G, int k, int flush,
     if (c < 64) {
         beg = __builtin_amdgcn_readlane(G.beg[0], l);
         cnt = __builtin_amdgcn_readlane(G.cnt[0], l);
-        first = __builtin_amdgcn_readlane(G.end[0], l);
+        first = __builtin_amdgcn_readlane(G.first[0], l);
     } else {
         beg = __builtin_amdgcn_readlane(G.beg[1], l);
         cnt = __builtin_amdgcn_readlane(G.cnt[1], l);
-        first = __builtin_amdgcn_readlane(G.end[1], l);
+        first = __builtin_amdgcn_readlane(G.first[1], l);
     }
-    first -= groups_of<COMP>(cnt, flush, gpb);
     const int i = k - first;
     int from = 0, at = 4 * i, upto = cnt;
     if constexpr (COMP) {
@@ -867,27 +873,23 @@ __device__ __forceinline__ void pair_terms(const Sep<MODE, 4> &d, const Coef &k,
     }
 }
 
-template <int MODE, bool COMP>
-__global__ void __launch_bounds__(kWideThreads)
-k_dense_wide(const DevBox *__restrict__ boxes, const Item *__restrict__ items,
-             const uint32_t *__restrict__ totals, uint32_t *counter,
-             const float4 *__restrict__ cot_sorted) {
-    // per buffer and group: f, then the three components of e, four pairs a lane
-    __shared__ float4 terms[2][kProducers][4][64];
-    __shared__ int ends[2][kProducers];
-    __shared__ int s_item;
+// The queue's items, by a workgroup of P + 3 waves.
+template <int MODE, bool COMP, int P>
+__device__ __forceinline__ void wide_items(WideSmem<P> &sm, const DevBox *__restrict__ boxes,
+                                           const Item *__restrict__ items, int nitems,
+                                           uint32_t *counter,
+                                           const float4 *__restrict__ cot_sorted) {
     const int lane = threadIdx.x & 63, wave = uni(threadIdx.x >> 6);
-    const int nitems = (int)totals[0];
     const int x = (int)(blockIdx.x % kXcds);   // one queue per XCD, as k_dense
     uint32_t *dq = counter + kQueueStride * x;
     for (;;) {
         if (threadIdx.x == 0) {
             const int t = (int)__hip_atomic_fetch_add(gp(dq), 1u, __ATOMIC_RELAXED,
                                                       __HIP_MEMORY_SCOPE_AGENT);
-            s_item = t * kXcds + x;   // few items: dealt singly
+            sm.item = t * kXcds + x;   // few items: dealt singly
         }
         __syncthreads();
-        const int itx = uni(s_item);
+        const int itx = uni(sm.item);
         __syncthreads();
         if (itx >= nitems) break;
         const gptr<const Item> ip = gp(items) + itx;
@@ -917,10 +919,12 @@ k_dense_wide(const DevBox *__restrict__ boxes, const Item *__restrict__ items,
             }
             G.end[0] = scan_lanes<64>(ng[0]);
             G.end[1] = scan_lanes<64>(ng[1]) + __builtin_amdgcn_readlane(G.end[0], 63);
+#pragma unroll
+            for (int h = 0; h < 2; ++h) G.first[h] = G.end[h] - ng[h];
         }
         const int ngroups = __builtin_amdgcn_readlane(G.end[1], 63);
-        const int rounds = (ngroups + kProducers - 1) / kProducers;
-        if (wave < kProducers) {
+        const int rounds = (ngroups + P - 1) / P;
+        if (wave < P) {
             const float4 oi = ld_global4((gfloat *)B.off, slot);
             float4 vi = make_float4(0.f, 0.f, 0.f, 0.f);
             if constexpr (MODE == 1)
@@ -944,7 +948,7 @@ k_dense_wide(const DevBox *__restrict__ boxes, const Item *__restrict__ items,
                     const Sep<MODE, 4> d = separations<MODE, 4>(rec, xs, ys, zs, vi);
                     const int count = gr.count;
                     const bool e = gr.ends;
-                    kg += kProducers;
+                    kg += P;
                     gr = group_of<COMP>(G, min(kg, ngroups - 1), flush, gpb, gpb_inv);
                     __builtin_amdgcn_sched_barrier(0);
                     rec = load_group<MODE>(src, gr.j, B.n);
@@ -959,31 +963,31 @@ k_dense_wide(const DevBox *__restrict__ boxes, const Item *__restrict__ items,
 #pragma unroll
                     for (int u = 1; u < 4; ++u)
                         if (u >= count) f[u] = ex[u] = ey[u] = ez[u] = 0.f;
-                    float4(*o)[64] = terms[t & 1][wave];
+                    float4(*o)[64] = sm.terms[t & 1][wave];
                     o[0][lane] = make_float4(f[0], f[1], f[2], f[3]);
                     o[1][lane] = make_float4(ex[0], ex[1], ex[2], ex[3]);
                     o[2][lane] = make_float4(ey[0], ey[1], ey[2], ey[3]);
                     o[3][lane] = make_float4(ez[0], ez[1], ez[2], ez[3]);
-                    if (lane == 0) ends[t & 1][wave] = e ? 1 : 0;
+                    if (lane == 0) sm.ends[t & 1][wave] = e ? 1 : 0;
                 }
                 __syncthreads();
             }
         } else {
-            const int comp = wave - kProducers;
+            const int comp = wave - P;
             const int dst = gp(B.order)[slot];
             float p = 0.f, sum = 0.f, low = 0.f;
             for (int t = 0; t <= rounds; ++t) {
                 if (t > 0) {
-                    const int buf = (t - 1) & 1, m = min(kProducers, ngroups - (t - 1) * kProducers);
-                    const int last = COMP ? ends[buf][lane < kProducers ? lane : 0] : 0;
-                    float4 f[kProducers], e[kProducers];
+                    const int buf = (t - 1) & 1, m = min(P, ngroups - (t - 1) * P);
+                    const int last = COMP ? sm.ends[buf][lane < P ? lane : 0] : 0;
+                    float4 f[P], e[P];
 #pragma unroll
-                    for (int i = 0; i < kProducers; ++i) {
-                        f[i] = terms[buf][i][0][lane];
-                        e[i] = terms[buf][i][1 + comp][lane];
+                    for (int i = 0; i < P; ++i) {
+                        f[i] = sm.terms[buf][i][0][lane];
+                        e[i] = sm.terms[buf][i][1 + comp][lane];
                     }
 #pragma unroll
-                    for (int i = 0; i < kProducers; ++i) {
+                    for (int i = 0; i < P; ++i) {
                         if (i < m) {
                             p = __builtin_fmaf(f[i].x, e[i].x, p);
                             p = __builtin_fmaf(f[i].y, e[i].y, p);
@@ -1004,6 +1008,17 @@ k_dense_wide(const DevBox *__restrict__ boxes, const Item *__restrict__ items,
                 gp(B.out)[3 * (int64_t)dst + comp] = (COMP ? sum - low : p) * B.scale;
         }
     }
+}
+
+constexpr int kProducers = 5;
+constexpr int kWideThreads = 64 * (kProducers + 3);
+template <int MODE, bool COMP>
+__global__ void __launch_bounds__(kWideThreads)
+k_dense_wide(const DevBox *__restrict__ boxes, const Item *__restrict__ items,
+             const uint32_t *__restrict__ totals, uint32_t *counter,
+             const float4 *__restrict__ cot_sorted) {
+    __shared__ WideSmem<kProducers> sm;
+    wide_items<MODE, COMP, kProducers>(sm, boxes, items, (int)totals[0], counter, cot_sorted);
 }
 
 // ------------------------------------------------------------------ light path
@@ -1121,22 +1136,23 @@ __device__ __forceinline__ void segment(const float4 *__restrict__ sx, const flo
     }
 }
 
-// NT threads share one item (256 for light items, 64 for narrow ones); cls
-// selects the item class: 1 light (items from the start of the array), 2
-// narrow (after the light ones).
-template <int MODE, bool COMP, int CAP, int NT>
-__global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(MODE == 0 ? 8 : 7)))
-k_light(const DevBox *__restrict__ boxes, const Item *__restrict__ all_items,
-        const uint32_t *__restrict__ totals, uint32_t *counter,
-        const float4 *__restrict__ cot_sorted, int cls) {
+// Items of one class by NT threads an item (256 for light items, 64 for narrow
+// ones), lane 0 .. NT-1, drawing from queue q; sync() is a barrier of the NT
+// threads.  cls selects the item class: 1 light (items from the start of the
+// array), 2 narrow (after the light ones).
+template <int MODE, bool COMP, int CAP, int NT, class Sync>
+__device__ __forceinline__ void light_items(LightSmem<MODE, CAP, NT> &sm, const int lane,
+                                            const int q, Sync &sync,
+                                            const DevBox *__restrict__ boxes,
+                                            const Item *__restrict__ all_items,
+                                            const uint32_t *__restrict__ totals, uint32_t *counter,
+                                            const float4 *__restrict__ cot_sorted, int cls) {
     static_assert(CAP % NT == 0, "a staging window is whole rounds of the workgroup");
     static_assert(NT % 64 == 0 && NT <= kLightThreads, "whole waves");
-    __shared__ LightSmem<MODE, CAP, NT> sm;
-    const int lane = threadIdx.x;   // 0 .. NT-1, all waves share the item
     const int nitems = (int)totals[cls];
     const gptr<const Item> items = gp(all_items) + (cls == 2 ? totals[1] : 0u);
 
-    // kQueues interleaved queues: workgroup w draws from queue q = w % kQueues
+    // kQueues interleaved queues: workgroup w of k_light draws from queue q = w % kQueues
     // (a single counter would cap the item rate at what one address sustains
     // for atomics).  The workgroups of queue q run on XCD q % 8, and the
     // queues of one XCD share blocks of up to kXcdBlock consecutive items (items
@@ -1145,7 +1161,6 @@ k_light(const DevBox *__restrict__ boxes, const Item *__restrict__ all_items,
     // its items in turn.  (q, k) -> item is one-to-one and increasing in k,
     // so the results do not depend on where the workgroups actually run;
     // only the L2 locality does.
-    const int q = (int)(blockIdx.x % kQueues);
     uint32_t *qc = counter + kQueueStride * q;
     const int xb = xcd_block_log2(nitems, kXcdBlock);
     auto queue_item = [q, xb](int kth) {
@@ -1163,7 +1178,7 @@ k_light(const DevBox *__restrict__ boxes, const Item *__restrict__ all_items,
         }
     }
     for (;;) {
-        __syncthreads();
+        sync();
         const int itx = uni(sm.item);
         if (itx >= nitems) break;
         const int ibox = uni(sm.ibox), cell0 = uni(sm.icell), chunk = uni(sm.ichunk);
@@ -1284,7 +1299,7 @@ k_light(const DevBox *__restrict__ boxes, const Item *__restrict__ all_items,
                 sm.total = tin + tout;
             }
         }
-        __syncthreads();
+        sync();
         int nbox = 0, ncell = 0, nchunk = 0;
         if (lane == 0 && nxt < nitems) {
             nbox = items[nxt].box;
@@ -1324,7 +1339,7 @@ k_light(const DevBox *__restrict__ boxes, const Item *__restrict__ all_items,
                 const int x = scan_lanes<(kWords <= 32 ? 32 : 64)>(c);
                 if (lane < kWords) sm.cum[lane] = kb + x - c;
             }
-            __syncthreads();
+            sync();
             int pos[kPer], d[kPer];
 #pragma unroll
             for (int i = 0; i < kPer; ++i) {
@@ -1364,7 +1379,7 @@ k_light(const DevBox *__restrict__ boxes, const Item *__restrict__ all_items,
                     sm.sx[d[i] - u0] = v;
                 }
             }
-            __syncthreads();
+            sync();
         };
 
         if (single) stage(0, total);
@@ -1373,7 +1388,7 @@ k_light(const DevBox *__restrict__ boxes, const Item *__restrict__ all_items,
         for (int u0 = 0; u0 < total; u0 += CAP) {
             const int u1 = min(total, u0 + CAP);
             if (!single) {
-                __syncthreads();
+                sync();
                 stage(u0, u1);
             }
             if (active) {
@@ -1391,7 +1406,7 @@ k_light(const DevBox *__restrict__ boxes, const Item *__restrict__ all_items,
         }
         // ---- fixed-order pairwise sum over slices: slice b adds slice b + half
         //      (TwoSum-compensated in the compensated mode); red overlays sx
-        __syncthreads();
+        sync();
         if constexpr (COMP) {
             sm.red[0][lane] = acc.x;
             sm.red[1][lane] = acc.y;
@@ -1404,7 +1419,7 @@ k_light(const DevBox *__restrict__ boxes, const Item *__restrict__ all_items,
             sm.red[1][lane] = acc.y;
             sm.red[2][lane] = acc.z;
         }
-        __syncthreads();
+        sync();
         for (int span = P; span > 1;) {
             const int half = (span + 1) >> 1;
             if (active && b < span - half) {
@@ -1423,7 +1438,7 @@ k_light(const DevBox *__restrict__ boxes, const Item *__restrict__ all_items,
                     }
                 }
             }
-            __syncthreads();
+            sync();
             span = half;
         }
         if (lane < g) {
@@ -1435,7 +1450,7 @@ k_light(const DevBox *__restrict__ boxes, const Item *__restrict__ all_items,
                 f = make_float3(sm.red[0][lane], sm.red[1][lane], sm.red[2][lane]);
             store(B, dst, f);
         }
-        __syncthreads();
+        sync();
         if (lane == 0) {
             sm.item = nxt;
             sm.ibox = nbox;
@@ -1443,6 +1458,98 @@ k_light(const DevBox *__restrict__ boxes, const Item *__restrict__ all_items,
             sm.ichunk = nchunk;
         }
     }
+}
+
+struct WorkgroupSync {
+    __device__ __forceinline__ void operator()() { __syncthreads(); }
+};
+
+template <int MODE, bool COMP, int CAP, int NT>
+__global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(MODE == 0 ? 8 : 7)))
+k_light(const DevBox *__restrict__ boxes, const Item *__restrict__ all_items,
+        const uint32_t *__restrict__ totals, uint32_t *counter,
+        const float4 *__restrict__ cot_sorted, int cls) {
+    __shared__ LightSmem<MODE, CAP, NT> sm;
+    WorkgroupSync sync;
+    light_items<MODE, COMP, CAP, NT>(sm, (int)threadIdx.x, (int)(blockIdx.x % kQueues), sync, boxes,
+                                     all_items, totals, counter, cot_sorted, cls);
+}
+
+// ------------------------------------------------------------------ small calls
+
+// The three item classes of a small call in one launch: workgroups of sixteen
+// waves take dense items (thirteen producers), then, each four waves by
+// themselves, light items, then, each wave by itself, narrow items, with the
+// windows, the threads an item and so the sums of the separate kernels.
+constexpr int kSmallProducers = 13;
+constexpr int kSmallThreads = 64 * (kSmallProducers + 3);
+constexpr int kQuarters = kSmallThreads / kLightThreads;
+
+// Barrier of the kLightThreads / 64 waves of a quarter, all of one workgroup
+// and so all resident: arrivals are counted in LDS, and each waits for the last
+// one of its own barrier (every wave passes the same barriers in order).
+struct QuarterSync {
+    uint32_t *arrived;
+    uint32_t expected = 0;
+    __device__ __forceinline__ void operator()() {
+        expected += kLightThreads / 64;
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+        if ((threadIdx.x & 63) == 0)
+            __hip_atomic_fetch_add(arrived, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        while (__hip_atomic_load(arrived, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) <
+               expected)
+            __builtin_amdgcn_s_sleep(1);
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+    }
+};
+// One wave: its LDS operations complete in order.
+struct WaveSync {
+    __device__ __forceinline__ void operator()() {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    }
+};
+
+template <int MODE>
+struct SmallSmem {
+    static constexpr int kLightCap = MODE == 0 ? 1024 : 768, kNarrowCap = MODE == 0 ? 256 : 192;
+    union {
+        WideSmem<kSmallProducers> wide;
+        union {
+            LightSmem<MODE, kLightCap, kLightThreads> light;
+            LightSmem<MODE, kNarrowCap, kNarrowThreads> narrow[kLightThreads / kNarrowThreads];
+        } part[kQuarters];
+    };
+    uint32_t arrived[kQuarters];
+};
+
+template <int MODE, bool COMP>
+__global__ void __launch_bounds__(kSmallThreads)
+k_small(const DevBox *__restrict__ boxes, const Item *__restrict__ dense,
+        const Item *__restrict__ light, const uint32_t *__restrict__ totals, uint32_t *counter,
+        const float4 *__restrict__ cot_sorted) {
+    typedef SmallSmem<MODE> Smem;
+    __shared__ __align__(16) char raw[sizeof(Smem)];
+    Smem &sm = *reinterpret_cast<Smem *>(raw);
+    if (threadIdx.x < kQuarters) sm.arrived[threadIdx.x] = 0u;
+    // (the barriers that end this also order the zeros before the quarters')
+    wide_items<MODE, COMP, kSmallProducers>(sm.wide, boxes, dense, (int)totals[0], counter,
+                                            cot_sorted);
+    const int quarter = uni(threadIdx.x / kLightThreads), wave = uni(threadIdx.x >> 6);
+    const int x = (int)(blockIdx.x % kXcds);   // queues x, x + 8, ... are XCD x's
+    auto &part = sm.part[quarter];
+    QuarterSync qsync{&sm.arrived[quarter]};
+    uint32_t *q = counter + kQueueStride * kXcds;
+    light_items<MODE, COMP, Smem::kLightCap, kLightThreads>(
+        part.light, (int)threadIdx.x % kLightThreads, x + kXcds * (quarter % (kQueues / kXcds)),
+        qsync, boxes, light, totals, q, cot_sorted, 1);
+    qsync();   // the light items' shared memory is free
+    WaveSync wsync;
+    light_items<MODE, COMP, Smem::kNarrowCap, kNarrowThreads>(
+        part.narrow[wave % (kLightThreads / kNarrowThreads)], (int)(threadIdx.x & 63),
+        x + kXcds * (wave % (kQueues / kXcds)), wsync, boxes, light, totals,
+        q + kQueueStride * kQueues, cot_sorted, 2);
 }
 
 // ------------------------------------------------------------------ launches
@@ -1581,6 +1688,27 @@ hipError_t launch_dense(const DevBox *d_boxes, const TilePlan &tp, const float4 
     return hipGetLastError();
 }
 
+// k_small takes calls of at most this many particles (with the default windows,
+// which it is built for).  Below, a call is bound by the host: a fork to two
+// streams and the joins take 50 us of it.  Above, a workgroup per CU is too few
+// for the dense items.  Whole calls, three kernels on three streams / k_small,
+// us, clustered: 1000 particles plain 82 / 28, VJP 65 / 37; 4096 92 / 48, 103 /
+// 60; 16384 107 / 60, 129 / 75; 50k 139 / 124, 179 / 177; 65k 210 / 224, 259 /
+// 267; uniform 32768 74 / 55, 94 / 80.
+constexpr int64_t kSmallMax = 60000;
+
+template <int MODE, bool COMP>
+hipError_t launch_small(const DevBox *d_boxes, const TilePlan &tp, const float4 *cot,
+                        hipStream_t s) {
+    static const int most =
+        (persistent_grid(k_small<MODE, COMP>, kSmallThreads) + kXcds - 1) / kXcds * kXcds;
+    const int grid = grid_for(most, tp.max_dense + tp.max_light, kXcds);
+    hipLaunchKernelGGL((k_small<MODE, COMP>), dim3(grid), dim3(kSmallThreads), 0, s, d_boxes,
+                       (const Item *)tp.dense, (const Item *)tp.light,
+                       (const uint32_t *)tp.totals, tp.counter, cot);
+    return hipGetLastError();
+}
+
 template <int MODE, bool COMP>
 hipError_t launch_force(const DevBox *d_boxes, const TilePlan &tp, const float4 *cot,
                         bool concurrent, hipStream_t s, const F4Plan *f4) {
@@ -1592,6 +1720,9 @@ hipError_t launch_force(const DevBox *d_boxes, const TilePlan &tp, const float4 
         if (f4 && (e = f4_ring_launch(d_boxes, *f4, COMP, s)) != hipSuccess) return e;
         return hipSuccess;
     }
+    if (!f4 && tp.particles <= kSmallMax && tp.light_window == kDefaultLightWindow &&
+        tp.narrow_window == kDefaultNarrowWindow)
+        return launch_small<MODE, COMP>(d_boxes, tp, cot, s);
     std::lock_guard<std::mutex> lk(g_side_mu);
     SideStream ss;
     if ((e = side_stream(ss)) != hipSuccess) return e;

@@ -366,6 +366,30 @@ def test_dense_items_of_small_and_large_calls_bitwise(law):
                                nfp.accel_vjp(two, [v, torch.ones_like(far).float()], 1.0, **kw)[0])
 
 
+@pytest.mark.parametrize("counts", [
+    [0] * 124 + [1], [3, 0, 11], [12, 40, 0, 25], [41, 64, 128],
+    [0, 1, 2, 5, 11, 12, 40, 41, 63, 64, 65, 76, 139, 700]],
+    ids=["one", "narrow", "light", "dense", "mixed"])
+def test_small_call_in_one_launch_equals_the_separate_kernels_bitwise(counts):
+    """The single kernel of a small call against the three kernels in turn:
+    every item class alone and together, queues that stay empty, cells of more
+    sources than a light or narrow window holds (700 of one cell), and other
+    windows, which take the separate kernels."""
+    K, L = 5, 1.0
+    pos = _gpu(_box_with_counts(K, L, counts, seed=31))
+    v = torch.from_numpy(gaussian_cotangent(len(pos), 32).astype(np.float32)).to(DEV)
+    for plummer in (False, True):
+        b = nfp.bin_particles(pos, K, L, 0.3 * L / K)
+        for windows in ((0, 0), (512, 128)):
+            b.set_tiles(nfp.Tiles(light_window=windows[0], narrow_window=windows[1]))
+            for comp in (False, True):
+                print(f"[small] {len(pos)} {plummer} {windows} {comp}", flush=True)
+                kw = dict(compensated=comp, plummer=plummer)
+                assert torch.equal(nfp.accel(b, 1.0, **kw), nfp.accel(b, 1.0, serial=True, **kw))
+                assert torch.equal(nfp.accel_vjp(b, v, 1.0, **kw),
+                                   nfp.accel_vjp(b, v, 1.0, serial=True, **kw))
+
+
 def test_tile_all_items_narrow():
     """A sparse box (at most 11 particles per cell): every item is narrow and
     the dense and light kernels find empty queues."""
