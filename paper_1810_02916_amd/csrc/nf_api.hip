@@ -21,14 +21,6 @@ int fail(int code, const std::string &msg) {
     return code;
 }
 
-// Descriptor bytes travel as a kernel argument (no host-to-device memcpy), so
-// every call is a pure sequence of kernel launches.  3840 bytes and the other
-// arguments fit the 4 KB that kernel arguments may take.
-constexpr int kChunkBytes = 3840;
-struct Chunk {
-    unsigned char bytes[kChunkBytes];
-};
-
 // The bytes to dst, and nzero words of zeros to zero.
 __global__ void __launch_bounds__(256)
 k_put_bytes(Chunk c, unsigned char *dst, int nbytes, uint32_t *zero, int nzero) {
@@ -91,8 +83,8 @@ struct Layout {
     std::vector<int64_t> base, cellbase;
     // workspace byte offsets
     size_t table_off = 0, table_bytes = 0;
-    size_t keys_off[2] = {0, 0}, vals_off[2] = {0, 0};
-    size_t hist_off = 0, cellcnt_off = 0, scan_off = 0;
+    size_t keys_off[2] = {0, 0}, rec_off[2] = {0, 0};
+    size_t hist_off = 0, digits_off = 0, bad_off = 0;
     size_t cot_off = 0, cellinfo_off = 0, bucket_off = 0, totals_off = 0, dense_off = 0,
            light_off = 0, counter_off = 0;
     size_t stepio_off = 0, cellstat_off = 0, partial_off = 0, partstat_off = 0;
@@ -106,10 +98,9 @@ struct Layout {
            f4tot_off = 0, f4items_off = 0, f4part_off = 0, f4blk_off = 0;
     uint32_t f4cap_slots = 0, f4cap_items = 0;
     size_t total = 0;
-    int64_t nblk = 0;
+    int64_t nblk = 0, pitch = 0;
     int passes = 0;
     int radix_bits = 8;
-    size_t offc_off = 0;
     int light_window = kDefaultLightWindow, narrow_window = kDefaultNarrowWindow;
 };
 
@@ -184,20 +175,16 @@ int validate(int nbox, const nf_box *boxes, Layout &L, uint32_t flags = 0) {
     for (int k = 0; k < 2; ++k) {
         L.keys_off[k] = o;
         o = align_up(o + 4 * (size_t)L.N, 256);
-        L.vals_off[k] = o;
-        o = align_up(o + 4 * (size_t)L.N, 256);
+        L.rec_off[k] = o;   // the second one from three passes on
+        if (k == 0 || L.passes > 2) o = align_up(o + 16 * (size_t)L.N, 256);
     }
-    L.offc_off = o;
-    o = align_up(o + 16 * (size_t)L.N, 256);
+    L.pitch = (L.nblk + 3) / 4 * 4;
     L.hist_off = o;
-    o = align_up(o + 4 * (size_t)(1 << L.radix_bits) * (size_t)L.nblk, 256);
-    L.cellcnt_off = o;
-    o = align_up(o + 4 * (size_t)(L.C + 1), 256);
-    L.scan_off = o;
-    const int64_t scan_words =
-        std::max(scan_scratch_words((int64_t)(1 << L.radix_bits) * L.nblk),
-                 scan_scratch_words(L.C + 1));
-    o = align_up(o + 4 * (size_t)scan_words, 256);
+    o = align_up(o + 4 * (size_t)(1 << L.radix_bits) * (size_t)L.pitch, 256);
+    L.digits_off = o;
+    o = align_up(o + 4 * (size_t)(1 << L.radix_bits), 256);
+    L.bad_off = o;
+    o = align_up(o + 4 * (size_t)nbox, 256);
     const size_t bin_end = o;
     // force scratch reuses the binning scratch region: the planner's tables
     // first, then the VJP's source records
@@ -409,27 +396,40 @@ int nf_bin_particles(int nbox, const nf_box *boxes, void *ws, size_t ws_bytes, v
         if ((rc = check_device(why))) return fail(rc, why);
         std::vector<DevBox> tab((size_t)nbox);
         for (int b = 0; b < nbox; ++b) fill_geometry(boxes[b], L, b, tab[b]);
+        const size_t tab_bytes = sizeof(DevBox) * tab.size();
         hipStream_t s = static_cast<hipStream_t>(stream);
         char *w = static_cast<char *>(ws);
         DevBox *d_tab = reinterpret_cast<DevBox *>(w + L.table_off);
-        hipError_t e = upload(tab.data(), sizeof(DevBox) * tab.size(), d_tab, s);
+        const bool small = bin_is_small(L.max_n, L.max_ncell);
+        const bool in_args = small && tab_bytes <= (size_t)kChunkBytes;
+        hipError_t e = in_args ? hipSuccess
+                               : upload(tab.data(), tab_bytes, d_tab, s,
+                                        reinterpret_cast<uint32_t *>(w + L.bad_off),
+                                        small ? 0 : nbox);
         if (e != hipSuccess) return fail(NF_EHIP, std::string("upload: ") + hipGetErrorString(e));
+        if (small) {
+            Chunk c;
+            if (in_args) std::memcpy(c.bytes, tab.data(), tab_bytes);
+            e = bin_small_launch(c, in_args ? nullptr : d_tab, nbox, s);
+            if (e != hipSuccess)
+                return fail(NF_EHIP, std::string("bin launch: ") + hipGetErrorString(e));
+            g_last_error.clear();
+            return NF_OK;
+        }
         BinPlan p;
         p.N = L.N;
-        p.C = L.C;
         p.max_n = L.max_n;
-        p.max_ncell = L.max_ncell;
         p.nblk = L.nblk;
+        p.pitch = L.pitch;
         p.passes = L.passes;
         p.radix_bits = L.radix_bits;
         for (int k = 0; k < 2; ++k) {
             p.sc.keys[k] = reinterpret_cast<uint32_t *>(w + L.keys_off[k]);
-            p.sc.vals[k] = reinterpret_cast<uint32_t *>(w + L.vals_off[k]);
+            p.sc.rec[k] = reinterpret_cast<float4 *>(w + L.rec_off[k]);
         }
-        p.sc.offc = reinterpret_cast<float4 *>(w + L.offc_off);
         p.sc.hist = reinterpret_cast<uint32_t *>(w + L.hist_off);
-        p.sc.cellcnt = reinterpret_cast<uint32_t *>(w + L.cellcnt_off);
-        p.scan_scratch = reinterpret_cast<uint32_t *>(w + L.scan_off);
+        p.sc.total = reinterpret_cast<uint32_t *>(w + L.digits_off);
+        p.sc.bad = reinterpret_cast<uint32_t *>(w + L.bad_off);
         e = bin_launch(d_tab, nbox, p, s);
         if (e != hipSuccess) return fail(NF_EHIP, std::string("bin launch: ") + hipGetErrorString(e));
         g_last_error.clear();

@@ -18,50 +18,11 @@ __global__ void k_fill_u32(uint32_t *p, int64_t count, uint32_t value) {
     for (; i < count; i += stride) p[i] = value;
 }
 
-// Zero each box's bad-particle counter.
-__global__ void k_bin_zero_status(const DevBox *boxes, int nbox) {
-    int b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b < nbox && boxes[b].nbad) boxes[b].nbad[0] = 0;
-}
-
-// ------------------------------------------------------------- cell keys
-
-// One thread per particle: linear cell id (in the box's key range), its
-// concatenated element index, and its float offsets and z cell in caller
-// order (the sort then moves 16 bytes per particle once, in k_bin_finish,
-// instead of recomputing them from the double positions).
-__global__ void __launch_bounds__(256) k_bin_keys(const DevBox *boxes, BinScratch sc) {
-    const DevBox &B = boxes[blockIdx.y];
-    int i = blockIdx.x * 256 + threadIdx.x;
-    if (i >= B.n) return;
-    int c[3];
-    float o[3];
-    bool ok = true;
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        double od;
-        ok &= cell_coord(B.pos[3 * (int64_t)i + a], B.kappa, B.K, c[a], od);
-        o[a] = (float)od;
-    }
-    if (!ok) {
-        c[0] = c[1] = c[2] = 0;
-        o[0] = o[1] = o[2] = 0.0f;
-        if (B.nbad) atomicAdd(B.nbad, 1);
-    }
-    uint32_t key = (uint32_t)B.cellbase + (uint32_t)((c[0] * B.K + c[1]) * B.K + c[2]);
-    int64_t g = B.base + i;
-    sc.keys[0][g] = key;
-    sc.offc[g] = make_float4(o[0], o[1], o[2], (float)c[2]);
-}
-
-// ------------------------------------------------------------- radix sort
-
-static_assert(kSortThreads == kScanThreads, "the sort's digit scan uses block_exclusive");
-
-// Block-wide exclusive scan of 256 thread totals; returns this thread's prefix
+// Block-wide exclusive scan of NT thread values; returns this thread's prefix
 // and the block total.
+template <int NT>
 __device__ __forceinline__ uint32_t block_exclusive(uint32_t v, uint32_t &total) {
-    __shared__ uint32_t wsum[kScanThreads / 64];
+    __shared__ uint32_t wsum[NT / 64];
     const int t = threadIdx.x, lane = t & 63, w = t >> 6;
     uint32_t x = v;
 #pragma unroll
@@ -73,7 +34,7 @@ __device__ __forceinline__ uint32_t block_exclusive(uint32_t v, uint32_t &total)
     __syncthreads();
     uint32_t wpre = 0, tot = 0;
 #pragma unroll
-    for (int q = 0; q < kScanThreads / 64; ++q) {
+    for (int q = 0; q < NT / 64; ++q) {
         uint32_t s = wsum[q];
         if (q < w) wpre += s;
         tot += s;
@@ -83,46 +44,146 @@ __device__ __forceinline__ uint32_t block_exclusive(uint32_t v, uint32_t &total)
     return wpre + x - v;
 }
 
-// Per-tile digit histogram, written digit-major: hist[d * nblk + tile].  The
-// count does not depend on the order within the tile, so a full tile is read
-// with 16-byte loads.
+// The box of concatenated element g: the last one that starts at or before it
+// (empty boxes share the start of the next one).
+__device__ __forceinline__ int box_of(const DevBox *boxes, int nbox, int64_t g) {
+    int lo = 0, hi = nbox;
+    while (hi - lo > 1) {
+        const int mid = (lo + hi) >> 1;
+        if (boxes[mid].base <= g) lo = mid; else hi = mid;
+    }
+    return lo;
+}
+
+// ------------------------------------------------------------- cell keys
+
+// Cell id and offsets of a particle of box B; false for one that has no cell
+// (cell 0, offsets 0).
+__device__ __forceinline__ bool particle_cell(const DevBox &B, const double (&x)[3], int &cell,
+                                              float (&o)[3]) {
+    int c[3];
+    bool ok = true;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        double od;
+        ok &= cell_coord(x[a], B.kappa, B.K, c[a], od);
+        o[a] = (float)od;
+    }
+    if (!ok) {
+        c[0] = c[1] = c[2] = 0;
+        o[0] = o[1] = o[2] = 0.0f;
+    }
+    cell = (c[0] * B.K + c[1]) * B.K + c[2];
+    return ok;
+}
+
+// The cell keys (cell id in the box's key range) of a tile of the concatenated
+// particles and the tile's histogram of the first digit, hist[d * pitch + tile].
+// Reading the keys back for that histogram took 10 us of 2.1M particles.
 template <int BITS>
 __global__ void __launch_bounds__(kSortThreads)
-k_radix_hist(const uint32_t *__restrict__ keys, int64_t N, int shift, int nblk,
-             uint32_t *__restrict__ hist) {
+k_bin_keys(const DevBox *__restrict__ boxes, int nbox, BinScratch sc, int64_t N, int pitch) {
     constexpr int R = 1 << BITS;
     __shared__ uint32_t cnt[R];
     const int t = threadIdx.x;
     for (int d = t; d < R; d += kSortThreads) cnt[d] = 0;
     __syncthreads();
-    const int w = t >> 6, lane = t & 63;
-    const int64_t base = (int64_t)blockIdx.x * kSortTile + w * (kSortTile / 4);
-    auto count = [&](bool valid, uint32_t key) {
-        uint32_t d = valid ? ((key >> shift) & (R - 1)) : 0u;
-        uint64_t m = match_digit<BITS>(valid, d);
-        if (valid && lane == 63 - __clzll(m)) atomicAdd(&cnt[d], (uint32_t)__popcll(m));
+    const int64_t tile0 = (int64_t)blockIdx.x * kSortTile;
+    const int64_t last = min(tile0 + kSortTile, N) - 1;
+    const int b0 = box_of(boxes, nbox, tile0), b1 = box_of(boxes, nbox, last);
+    double x[kSortItems][3];
+    auto load = [&](const DevBox &B, int64_t g, double (&p)[3]) {
+        const gptr<const double> q = gp(B.pos) + 3 * (g - B.base);
+#pragma unroll
+        for (int a = 0; a < 3; ++a) p[a] = q[a];
     };
-    if ((int64_t)(blockIdx.x + 1) * kSortTile <= N) {
-        const uint4 *k4 = reinterpret_cast<const uint4 *>(keys + base);
-        uint4 q[kSortItems / 4];
+    auto key = [&](const DevBox &B, int b, int64_t g, const double (&p)[3]) {
+        int cell;
+        float o[3];
+        if (!particle_cell(B, p, cell, o)) atomicAdd(&sc.bad[b], 1u);
+        const uint32_t k = (uint32_t)B.cellbase + (uint32_t)cell;
+        gp(sc.keys[0])[g] = k;
+        atomicAdd(&cnt[k & (R - 1)], 1u);
+    };
+    if (b0 == b1) {   // the common tile: one box, its descriptor in scalar registers
+        const DevBox &B = boxes[b0];
 #pragma unroll
-        for (int k = 0; k < kSortItems / 4; ++k) q[k] = k4[k * 64 + lane];
+        for (int k = 0; k < kSortItems; ++k) {
+            const int64_t g = tile0 + k * kSortThreads + t;
+            load(B, min(g, last), x[k]);
+        }
 #pragma unroll
-        for (int k = 0; k < kSortItems / 4; ++k) {
-            count(true, q[k].x);
-            count(true, q[k].y);
-            count(true, q[k].z);
-            count(true, q[k].w);
+        for (int k = 0; k < kSortItems; ++k) {
+            const int64_t g = tile0 + k * kSortThreads + t;
+            if (g <= last) key(B, b0, g, x[k]);
         }
     } else {
         for (int k = 0; k < kSortItems; ++k) {
-            int64_t idx = base + k * 64 + lane;
-            bool valid = idx < N;
-            count(valid, valid ? keys[idx] : 0u);
+            const int64_t g = tile0 + k * kSortThreads + t;
+            if (g > last) break;
+            const int b = box_of(boxes, nbox, g);
+            load(boxes[b], g, x[0]);
+            key(boxes[b], b, g, x[0]);
         }
     }
     __syncthreads();
-    for (int d = t; d < R; d += kSortThreads) hist[(int64_t)d * nblk + blockIdx.x] = cnt[d];
+    for (int d = t; d < R; d += kSortThreads)
+        gp(sc.hist)[(int64_t)d * pitch + blockIdx.x] = cnt[d];
+}
+
+// ------------------------------------------------------------- radix sort
+
+// The histogram of a later digit; the count does not depend on the order
+// within the tile, so a thread takes four consecutive keys by one load.
+template <int BITS>
+__global__ void __launch_bounds__(kSortThreads)
+k_radix_hist(const uint32_t *__restrict__ keys, int64_t N, int shift, int pitch,
+             uint32_t *__restrict__ hist) {
+    constexpr int R = 1 << BITS;
+    static_assert(kSortItems == 4, "one 16-byte load per thread");
+    __shared__ uint32_t cnt[R];
+    const int t = threadIdx.x;
+    for (int d = t; d < R; d += kSortThreads) cnt[d] = 0;
+    __syncthreads();
+    const int64_t g = (int64_t)blockIdx.x * kSortTile + 4 * t;
+    if (g + 4 <= N) {
+        const uint4 q = *reinterpret_cast<const uint4 *>(keys + g);
+        atomicAdd(&cnt[(q.x >> shift) & (R - 1)], 1u);
+        atomicAdd(&cnt[(q.y >> shift) & (R - 1)], 1u);
+        atomicAdd(&cnt[(q.z >> shift) & (R - 1)], 1u);
+        atomicAdd(&cnt[(q.w >> shift) & (R - 1)], 1u);
+    } else {
+        for (int64_t i = g; i < N; ++i) atomicAdd(&cnt[(keys[i] >> shift) & (R - 1)], 1u);
+    }
+    __syncthreads();
+    for (int d = t; d < R; d += kSortThreads) hist[(int64_t)d * pitch + blockIdx.x] = cnt[d];
+}
+
+// One workgroup per digit: its row of tile counts to exclusive prefixes over
+// the tiles, and its total.  (A scan over all counts takes two launches.)
+__global__ void __launch_bounds__(kScanThreads)
+k_scan_rows(uint32_t *__restrict__ hist, int nblk, int pitch, uint32_t *__restrict__ total) {
+    constexpr int kPer = 4;
+    uint32_t *row = hist + (int64_t)blockIdx.x * pitch;
+    uint32_t run = 0;
+    for (int b0 = 0; b0 < nblk; b0 += kPer * kScanThreads) {
+        const int b = b0 + kPer * (int)threadIdx.x;
+        uint32_t v[kPer], s = 0;
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) {
+            v[i] = b + i < nblk ? row[b + i] : 0u;
+            s += v[i];
+        }
+        uint32_t all;
+        uint32_t x = block_exclusive<kScanThreads>(s, all) + run;
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) {
+            if (b + i < nblk) row[b + i] = x;
+            x += v[i];
+        }
+        run += all;
+    }
+    if (threadIdx.x == 0) total[blockIdx.x] = run;
 }
 
 // The tile of workgroup b when each of the 8 XCDs (workgroups are dealt to
@@ -132,101 +193,182 @@ __device__ __forceinline__ int xcd_tile(int b, int nb) {
     return x * per + min(x, rem) + j;
 }
 
+// Rank of a wave's key among the wave's keys of the same digit so far:
+// "earlier round, then lower lane" is input order.  cnt: the wave's counters.
+template <int BITS>
+__device__ __forceinline__ uint32_t wave_rank(uint16_t *cnt, bool valid, uint32_t d, int lane,
+                                              uint64_t below) {
+    const uint64_t m = match_digit<BITS>(valid, d);
+    const uint32_t before = cnt[d];
+    __builtin_amdgcn_wave_barrier();
+    if (valid && lane == 63 - __clzll(m)) cnt[d] = (uint16_t)(before + (uint32_t)__popcll(m));
+    __builtin_amdgcn_wave_barrier();
+    return before + (uint32_t)__popcll(m & below);
+}
+
 // Stable scatter of one tile, workgroup b taking tile xcd_tile(b): the
 // neighbouring output runs of a digit (consecutive tiles) then meet whole in
-// one XCD's L2 instead of as line fragments in several.  Wave w owns the contiguous quarter
-// [w*1024, (w+1)*1024) of the tile and walks it in rounds of 64, so
-// "earlier round, then lower lane, then lower wave" is input order; that
-// gives every key its rank within the tile's run of its digit.  The tile is
-// then reordered by digit in LDS and written out slot by slot, so that the
-// lanes of a wave store consecutive addresses of one output run.  The first
-// pass (vals_in null) takes the element index as its value.
-template <int BITS>
+// one XCD's L2 instead of as line fragments in several.  Wave w owns a
+// contiguous part of the tile and walks it in rounds of 64, so "earlier round,
+// then lower lane, then lower wave" is input order; that gives every key its
+// rank within the tile's run of its digit.  The tile is then reordered by digit
+// in LDS and written out slot by slot, so that the lanes of a wave store
+// consecutive addresses of one output run.
+//
+// A key travels with its particle's record: the three offsets and the
+// concatenated index.  The first pass makes the records from the positions,
+// the last one writes the boxes' offsets and order.  Moving 16 bytes a pass in
+// runs is cheaper than gathering them once at the end, a random line per
+// particle, of which the last kernel took 44 us: binning 2.1M clustered particles
+// 148 -> 86 us, 16.8M (three passes) 947 -> 758.
+//
+// total null: few tiles, and every workgroup adds up the digits' counts (rows
+// of hist) itself; else hist holds the scanned rows and total their sums.
+// 50 KB of LDS, three workgroups a CU.
+template <int BITS, bool FIRST, bool LAST>
 __global__ void __launch_bounds__(kSortThreads)
-k_radix_scatter(const uint32_t *__restrict__ keys_in, const uint32_t *__restrict__ vals_in,
-                uint32_t *__restrict__ keys_out, uint32_t *__restrict__ vals_out,
-                int64_t N, int shift, int nblk, const uint32_t *__restrict__ hist_scan) {
+k_radix_scatter(const DevBox *__restrict__ boxes, int nbox, const uint32_t *__restrict__ keys_in,
+                const float4 *__restrict__ rec_in, uint32_t *__restrict__ keys_out,
+                float4 *__restrict__ rec_out, int64_t N, int shift, int nblk, int pitch,
+                const uint32_t *__restrict__ hist, const uint32_t *__restrict__ total) {
     constexpr int R = 1 << BITS;
-    constexpr int DPT = R / kSortThreads;   // digits per thread in the digit scan
-    static_assert(R % kSortThreads == 0, "radix must be a multiple of the block size");
-    __shared__ uint32_t gshift[R];        // output slot of the tile's local slot 0, per digit
-    __shared__ uint32_t wcnt[4][R];
+    constexpr int kWaves = kSortThreads / 64, kWaveKeys = kSortTile / kWaves;
+    static_assert(R <= kSortThreads, "a thread per digit in the digit scan");
+    __shared__ uint32_t gshift[R];   // output slot of the tile's local slot 0, per digit
+    __shared__ uint16_t wcnt[kWaves][R];
     __shared__ uint32_t skey[kSortTile];
-    __shared__ uint32_t sval[kSortTile];
+    __shared__ float4 srec[kSortTile];
     const int t = threadIdx.x;
     const int w = t >> 6, lane = t & 63;
     for (int d = t; d < R; d += kSortThreads) {
 #pragma unroll
-        for (int q = 0; q < 4; ++q) wcnt[q][d] = 0;
+        for (int q = 0; q < kWaves; ++q) wcnt[q][d] = 0;
     }
     __syncthreads();
 
     const uint64_t below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
     const int tile = xcd_tile((int)blockIdx.x, nblk);
     const int64_t tile0 = (int64_t)tile * kSortTile;
-    const int64_t base = tile0 + w * (kSortTile / 4);
-    uint32_t kk[kSortItems], vv[kSortItems], rk[kSortItems];
+    const int64_t last = min(tile0 + kSortTile, N) - 1;
+    const int64_t base = tile0 + w * kWaveKeys + lane;
+    uint32_t kk[kSortItems], rk[kSortItems];
+    float4 rec[kSortItems];
 #pragma unroll
-    for (int k = 0; k < kSortItems; ++k) {
-        int64_t idx = base + k * 64 + lane;
-        bool valid = idx < N;
-        uint32_t key = valid ? keys_in[idx] : 0u;
-        uint32_t val = valid ? (vals_in ? vals_in[idx] : (uint32_t)idx) : 0u;
-        uint32_t d = (key >> shift) & (R - 1);
-        uint64_t m = match_digit<BITS>(valid, d);
-        uint32_t before = wcnt[w][d];
-        __builtin_amdgcn_wave_barrier();
-        rk[k] = before + (uint32_t)__popcll(m & below);
-        if (valid && lane == 63 - __clzll(m)) wcnt[w][d] = before + (uint32_t)__popcll(m);
-        __builtin_amdgcn_wave_barrier();
-        kk[k] = key;
-        vv[k] = val;
+    for (int k = 0; k < kSortItems; ++k) kk[k] = gp(keys_in)[min(base + k * 64, last)];
+    if constexpr (FIRST) {
+        const int b0 = box_of(boxes, nbox, tile0), b1 = box_of(boxes, nbox, last);
+        auto load = [&](const DevBox &B, int64_t g, double (&x)[3]) {
+            const gptr<const double> q = gp(B.pos) + 3 * (g - B.base);
+#pragma unroll
+            for (int a = 0; a < 3; ++a) x[a] = q[a];
+        };
+        auto record = [&](const DevBox &B, int64_t g, const double (&x)[3]) {
+            float o[3];
+            bool ok = true;
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+                double od, f;
+                ok &= cell_offset(x[a], B.kappa, f, od);
+                o[a] = (float)od;
+            }
+            return make_float4(ok ? o[0] : 0.f, ok ? o[1] : 0.f, ok ? o[2] : 0.f,
+                               __uint_as_float((uint32_t)g));
+        };
+        if (b0 == b1) {
+            const DevBox &B = boxes[b0];
+            double x[kSortItems][3];
+#pragma unroll
+            for (int k = 0; k < kSortItems; ++k) load(B, min(base + k * 64, last), x[k]);
+#pragma unroll
+            for (int k = 0; k < kSortItems; ++k) rec[k] = record(B, min(base + k * 64, last), x[k]);
+        } else {
+#pragma unroll
+            for (int k = 0; k < kSortItems; ++k) {
+                const int64_t g = min(base + k * 64, last);
+                const DevBox &B = boxes[box_of(boxes, nbox, g)];
+                double x[3];
+                load(B, g, x);
+                rec[k] = record(B, g, x);
+            }
+        }
+    } else {
+#pragma unroll
+        for (int k = 0; k < kSortItems; ++k) {
+            const nf_v4f r = ld_g4(rec_in, (uint64_t)min(base + k * 64, last));
+            rec[k] = make_float4(r.x, r.y, r.z, r.w);
+        }
     }
+#pragma unroll
+    for (int k = 0; k < kSortItems; ++k)
+        rk[k] = wave_rank<BITS>(wcnt[w], base + k * 64 <= last, (kk[k] >> shift) & (R - 1), lane,
+                                below);
     __syncthreads();
     {   // per digit: exclusive prefix over the waves, then over the digits
-        uint32_t tot[DPT], sum = 0;
+        uint32_t sum = 0, before = 0, all = 0;
+        const int d = t;
+        if (d < R) {
 #pragma unroll
-        for (int j = 0; j < DPT; ++j) {
-            const int d = t * DPT + j;
-            uint32_t s = 0;
+            for (int q = 0; q < kWaves; ++q) sum += wcnt[q][d];
+            const uint32_t *row = hist + (int64_t)d * pitch;
+            if (total) {
+                before = row[tile];
+                all = total[d];
+            } else {
+                for (int b = 0; b < nblk; b += 4) {   // rows are padded to whole groups
+                    const uint4 c = *reinterpret_cast<const uint4 *>(row + b);
+                    const uint32_t v[4] = {c.x, c.y, c.z, c.w};
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                uint32_t c = wcnt[q][d];
-                wcnt[q][d] = s;
-                s += c;
+                    for (int i = 0; i < 4; ++i) {
+                        if (b + i < nblk) all += v[i];
+                        if (b + i < tile) before += v[i];
+                    }
+                }
             }
-            tot[j] = s;
-            sum += s;
         }
-        uint32_t all;
-        uint32_t run = block_exclusive(sum, all);
+        uint32_t unused;
+        uint32_t run = block_exclusive<kSortThreads>(sum, unused);
+        const uint32_t first = block_exclusive<kSortThreads>(all, unused);
+        if (d < R) {
+            gshift[d] = first + before - run;
 #pragma unroll
-        for (int j = 0; j < DPT; ++j) {
-            const int d = t * DPT + j;
-#pragma unroll
-            for (int q = 0; q < 4; ++q) wcnt[q][d] += run;
-            gshift[d] = hist_scan[(int64_t)d * nblk + tile] - run;
-            run += tot[j];
+            for (int q = 0; q < kWaves; ++q) {
+                const uint32_t c = wcnt[q][d];
+                wcnt[q][d] = (uint16_t)run;
+                run += c;
+            }
         }
     }
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < kSortItems; ++k) {
-        if (base + k * 64 + lane < N) {
-            uint32_t d = (kk[k] >> shift) & (R - 1);
-            uint32_t slot = wcnt[w][d] + rk[k];
+        if (base + k * 64 <= last) {
+            const uint32_t slot = wcnt[w][(kk[k] >> shift) & (R - 1)] + rk[k];
             skey[slot] = kk[k];
-            sval[slot] = vv[k];
+            srec[slot] = rec[k];
         }
     }
     __syncthreads();
-    const int cnt = (int)min<int64_t>(kSortTile, N - tile0);
-    for (int j = t; j < cnt; j += kSortThreads) {
+    const int cnt = (int)(last - tile0) + 1;
+#pragma unroll
+    for (int k = 0; k < kSortItems; ++k) {
+        const int j = t + k * kSortThreads;
+        if (j >= cnt) break;
         const uint32_t key = skey[j];
+        const float4 r = srec[j];
         const uint32_t dst = gshift[(key >> shift) & (R - 1)] + (uint32_t)j;
-        if (dst < (uint64_t)N) {   // always true for a consistent histogram
-            keys_out[dst] = key;
-            vals_out[dst] = sval[j];
+        if (dst >= (uint64_t)N) continue;   // never for a consistent histogram
+        gp(keys_out)[dst] = key;
+        if constexpr (LAST) {
+            const DevBox &B = boxes[box_of(boxes, nbox, (int64_t)dst)];
+            const int64_t i = (int64_t)__float_as_uint(r.w) - B.base;
+            const int64_t slot = (int64_t)dst - B.base;
+            if (slot < B.n) {   // always true for a consistent sort
+                const int z = (int)((key - (uint32_t)B.cellbase) % (uint32_t)B.K);
+                st_g4(B.off, (uint64_t)slot, r.x, r.y, r.z, (float)z);
+                gp(B.order)[slot] = (i >= 0 && i < B.n) ? (int)i : 0;   // likewise
+            }
+        } else {
+            st_g4(rec_out, dst, r.x, r.y, r.z, r.w);
         }
     }
 }
@@ -244,7 +386,7 @@ k_scan_reduce(const uint32_t *__restrict__ in, int64_t M, uint32_t *__restrict__
         if (i < M) s += in[i];
     }
     uint32_t tot;
-    block_exclusive(s, tot);
+    block_exclusive<kScanThreads>(s, tot);
     if (threadIdx.x == 0) sums[blockIdx.x] = tot;
 }
 
@@ -262,7 +404,7 @@ __device__ __forceinline__ void scan_tile(const uint32_t *in, uint32_t *out, int
         s += v[k];
     }
     uint32_t tot;
-    uint32_t run = block_exclusive(s, tot) + offset;
+    uint32_t run = block_exclusive<kScanThreads>(s, tot) + offset;
 #pragma unroll
     for (int k = 0; k < kScanItems; ++k) {
         int64_t i = base + k;
@@ -285,43 +427,161 @@ k_scan_down_sums(uint32_t *data, int64_t M, const uint32_t *__restrict__ sums) {
     uint32_t part = 0;
     for (int i = threadIdx.x; i < (int)blockIdx.x; i += kScanThreads) part += sums[i];
     uint32_t before;
-    block_exclusive(part, before);
+    block_exclusive<kScanThreads>(part, before);
     scan_tile(data, data, M, before);
 }
 
 // ------------------------------------------------------------- cell starts
 
-// first[k] = the first sorted slot whose key is >= k, for k = 0 .. C (the
-// exclusive scan of the cell counts), from the sorted keys: slot s writes
-// the keys in (key[s-1], key[s]], slot N the keys after the last one.  Keys
-// are non-decreasing, so every k is written exactly once; no atomics.
-__global__ void __launch_bounds__(256)
-k_cell_first(const uint32_t *__restrict__ keys, int64_t N, int64_t C,
-             uint32_t *__restrict__ first) {
-    for (int64_t s = (int64_t)blockIdx.x * 256 + threadIdx.x; s <= N;
-         s += (int64_t)gridDim.x * 256) {
-        const int64_t lo = s == 0 ? 0 : (int64_t)keys[s - 1] + 1;
-        const int64_t hi = s == N ? C : (int64_t)keys[s];
-        for (int64_t k = lo; k <= hi; ++k) first[k] = (uint32_t)s;
+// cell_start[c] = the first slot whose cell is >= c, for c = 0 .. ncell: slot s
+// (0 .. n) writes the cells in (cell of slot s-1, cell of slot s], slot n the
+// cells after the last one.  Every c is written exactly once.  The lanes of a
+// wave call this together (slots above n write nothing); a long run of empty cells is
+// written by the whole wave.
+template <class CellOf>
+__device__ __forceinline__ void write_cell_starts(int32_t *cell_start, int n, int ncell,
+                                                  int64_t slot, CellOf cell_of) {
+    const int lane = threadIdx.x & 63, s = (int)min(slot, (int64_t)n);
+    int lo = 0, hi = -1;
+    if (slot <= n) {
+        lo = s == 0 ? 0 : cell_of(s - 1) + 1;
+        hi = s == n ? ncell : cell_of(s);
+    }
+    gptr<int32_t> out = gp(cell_start);
+    uint64_t longs = __ballot(hi - lo >= 8);
+    if (hi - lo < 8)
+        for (int c = lo; c <= hi; ++c) out[c] = s;
+    while (longs) {
+        const int l = __ffsll((unsigned long long)longs) - 1;
+        longs &= longs - 1;
+        const int a = __builtin_amdgcn_readlane(lo, l), b = __builtin_amdgcn_readlane(hi, l);
+        const int v = __builtin_amdgcn_readlane(s, l);
+        for (int64_t c = (int64_t)a + lane; c <= b; c += 64) out[c] = v;
     }
 }
 
-// ------------------------------------------------------------- finish
-
-// Per box: cell_start from the first slots of its cells, order from the
-// sorted element indices, and the float offsets gathered from caller order.
+// Per box: cell_start from the sorted keys, and the count of bad particles.
 __global__ void __launch_bounds__(256)
-k_bin_finish(const DevBox *boxes, const uint32_t *__restrict__ cellscan,
-             const uint32_t *__restrict__ vals_sorted, const float4 *__restrict__ offc) {
+k_bin_cells(const DevBox *__restrict__ boxes, const uint32_t *__restrict__ keys,
+            const uint32_t *__restrict__ bad) {
     const DevBox &B = boxes[blockIdx.y];
-    int t = blockIdx.x * 256 + threadIdx.x;
-    if (t <= B.ncell) B.cell_start[t] = (int32_t)((int64_t)cellscan[B.cellbase + t] - B.base);
-    if (t < B.n) {
-        int64_t gi = (int64_t)vals_sorted[B.base + t] - B.base;
-        int i = (gi >= 0 && gi < B.n) ? (int)gi : 0;   // always in range for a valid sort
-        B.order[t] = i;
-        B.off[t] = offc[B.base + i];
+    if ((int64_t)blockIdx.x * 256 > B.n) return;
+    const int64_t s = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    const gptr<const uint32_t> k = gp(keys) + B.base;
+    const uint32_t c0 = (uint32_t)B.cellbase;
+    write_cell_starts(B.cell_start, B.n, B.ncell, s, [&](int i) { return (int)(k[i] - c0); });
+    if (s == 0 && B.nbad) B.nbad[0] = (int32_t)bad[blockIdx.y];
+}
+
+// ------------------------------------------------------------- small boxes
+
+// A whole box of at most kBinSmallN particles and kBinSmallCells cells by one
+// workgroup: the same stable sort with the keys in LDS.  The descriptors come as
+// a kernel argument (d_boxes null) or from memory.  Such a call was bound by its
+// eight launches: 1000 particles 32 -> 8 us (14 by the tiled sort in four
+// launches), 4096 29 -> 15 (17); one workgroup is slower above.
+template <int BITS>
+__device__ __forceinline__ void small_pass(int shift, int n, int rounds, int first, int lane,
+                                           uint64_t below, uint16_t *wcnt,
+                                           uint32_t *skey, uint16_t *sidx,
+                                           uint32_t (&kk)[kBinSmallItems],
+                                           uint32_t (&ix)[kBinSmallItems]) {
+    constexpr int R = 1 << BITS, kWaves = kBinSmallThreads / 64;
+    const int t = threadIdx.x, w = t >> 6;
+    for (int d = t; d < R * kWaves; d += kBinSmallThreads) wcnt[d] = 0;
+    __syncthreads();
+    uint32_t rk[kBinSmallItems];
+#pragma unroll
+    for (int k = 0; k < kBinSmallItems; ++k)
+        if (k < rounds)
+            rk[k] = wave_rank<BITS>(wcnt + w * R, first + k * 64 < n, (kk[k] >> shift) & (R - 1), lane,
+                                    below);
+    __syncthreads();
+    uint32_t sum = 0, all;
+    if (t < R)
+#pragma unroll
+        for (int q = 0; q < kWaves; ++q) sum += wcnt[q * R + t];
+    uint32_t run = block_exclusive<kBinSmallThreads>(sum, all);
+    if (t < R)
+#pragma unroll
+        for (int q = 0; q < kWaves; ++q) {
+            const uint32_t c = wcnt[q * R + t];
+            wcnt[q * R + t] = (uint16_t)run;
+            run += c;
+        }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kBinSmallItems; ++k)
+        if (k < rounds && first + k * 64 < n) {
+            const uint32_t slot = wcnt[w * R + ((kk[k] >> shift) & (R - 1))] + rk[k];
+            skey[slot] = kk[k];
+            sidx[slot] = (uint16_t)ix[k];
+        }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kBinSmallItems; ++k)
+        if (k < rounds && first + k * 64 < n) {
+            kk[k] = skey[first + k * 64];
+            ix[k] = sidx[first + k * 64];
+        }
+}
+
+__global__ void __launch_bounds__(kBinSmallThreads)
+k_bin_small(Chunk c, const DevBox *__restrict__ d_boxes) {
+    constexpr int kBits = 8, kWaves = kBinSmallThreads / 64;
+    __shared__ uint16_t wcnt[kWaves << (kBits + 1)];
+    __shared__ uint32_t skey[kBinSmallN];
+    __shared__ uint16_t sidx[kBinSmallN], slot_of[kBinSmallN];
+    __shared__ int nbad;
+    const DevBox &B = d_boxes ? d_boxes[blockIdx.x]
+                              : reinterpret_cast<const DevBox *>(c.bytes)[blockIdx.x];
+    const int n = B.n, t = threadIdx.x, lane = t & 63;
+    const uint64_t below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+    // wave w owns the particles [64 w rounds, 64 (w + 1) rounds)
+    const int rounds = (n + kBinSmallThreads - 1) / kBinSmallThreads;
+    const int first = (t >> 6) * 64 * rounds + lane;
+    if (t == 0) nbad = 0;
+    __syncthreads();
+    uint32_t kk[kBinSmallItems], ix[kBinSmallItems];
+    float off[kBinSmallItems][3];
+    int z[kBinSmallItems];
+#pragma unroll
+    for (int k = 0; k < kBinSmallItems; ++k) {
+        const int i = first + k * 64;
+        kk[k] = ix[k] = 0u;
+        if (k < rounds && i < n) {
+            const gptr<const double> p = gp(B.pos) + 3 * (int64_t)i;
+            const double x[3] = {p[0], p[1], p[2]};
+            int cell;
+            if (!particle_cell(B, x, cell, off[k])) atomicAdd(&nbad, 1);
+            kk[k] = (uint32_t)cell;
+            ix[k] = (uint32_t)i;
+            z[k] = cell % B.K;
+        }
     }
+    if ((B.ncell - 1) >> kBits == 1)   // one pass of nine bits
+        small_pass<kBits + 1>(0, n, rounds, first, lane, below, wcnt, skey, sidx, kk, ix);
+    else
+        for (int shift = 0; shift == 0 || (B.ncell - 1) >> shift; shift += kBits)
+            small_pass<kBits>(shift, n, rounds, first, lane, below, wcnt, skey, sidx, kk, ix);
+#pragma unroll
+    for (int k = 0; k < kBinSmallItems; ++k) {
+        const int s = first + k * 64;
+        if (k < rounds && s < n) {
+            gp(B.order)[s] = (int)ix[k];
+            slot_of[ix[k]] = (uint16_t)s;
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kBinSmallItems; ++k) {
+        const int i = first + k * 64;
+        if (k < rounds && i < n)
+            st_g4(B.off, slot_of[i], off[k][0], off[k][1], off[k][2], (float)z[k]);
+    }
+    for (int s0 = 0; s0 <= n; s0 += kBinSmallThreads)
+        write_cell_starts(B.cell_start, n, B.ncell, s0 + t, [&](int i) { return (int)skey[i]; });
+    if (t == 0 && B.nbad) B.nbad[0] = nbad;
 }
 
 // ------------------------------------------------------------- host driver
@@ -368,51 +628,64 @@ hipError_t fill_u32(uint32_t *p, int64_t count, uint32_t value, hipStream_t s) {
 }
 
 template <int BITS>
-static hipError_t sort_passes(const BinPlan &p, hipStream_t s) {
+static hipError_t sort_passes(const DevBox *d_boxes, int nbox, const BinPlan &p, hipStream_t s) {
     hipError_t e;
+    const dim3 tiles((unsigned)p.nblk), threads(kSortThreads);
+    const int pitch = (int)p.pitch;
+    // The scatter of few tiles adds up the rows itself instead of a scan: 32768
+    // particles 29 -> 25 us, 131k (64 tiles) equal, 262k 33 -> 39.
+    const bool scan = p.nblk > kRowTiles;
     int src = 0;
     for (int pass = 0; pass < p.passes; ++pass) {
         const int shift = pass * BITS;
-        hipLaunchKernelGGL(k_radix_hist<BITS>, dim3((unsigned)p.nblk), dim3(kSortThreads), 0, s,
-                           p.sc.keys[src], p.N, shift, (int)p.nblk, p.sc.hist);
+        const bool first = pass == 0, last = pass + 1 == p.passes;
+        if (first)
+            hipLaunchKernelGGL(k_bin_keys<BITS>, tiles, threads, 0, s, d_boxes, nbox, p.sc, p.N,
+                               pitch);
+        else
+            hipLaunchKernelGGL(k_radix_hist<BITS>, tiles, threads, 0, s,
+                               (const uint32_t *)p.sc.keys[src], p.N, shift, pitch, p.sc.hist);
         if ((e = hipGetLastError()) != hipSuccess) return e;
-        if ((e = scan_exclusive(p.sc.hist, (int64_t)(1 << BITS) * p.nblk, p.scan_scratch, s)) !=
-            hipSuccess)
-            return e;
-        hipLaunchKernelGGL(k_radix_scatter<BITS>, dim3((unsigned)p.nblk), dim3(kSortThreads), 0, s,
-                           p.sc.keys[src], pass == 0 ? (const uint32_t *)nullptr : p.sc.vals[src],
-                           p.sc.keys[src ^ 1], p.sc.vals[src ^ 1], p.N, shift, (int)p.nblk,
-                           p.sc.hist);
+        if (scan) {
+            hipLaunchKernelGGL(k_scan_rows, dim3(1 << BITS), dim3(kScanThreads), 0, s, p.sc.hist,
+                               (int)p.nblk, pitch, p.sc.total);
+            if ((e = hipGetLastError()) != hipSuccess) return e;
+        }
+        auto *scatter = first ? (last ? k_radix_scatter<BITS, true, true>
+                                      : k_radix_scatter<BITS, true, false>)
+                              : (last ? k_radix_scatter<BITS, false, true>
+                                      : k_radix_scatter<BITS, false, false>);
+        hipLaunchKernelGGL(scatter, tiles, threads, 0, s, d_boxes, nbox,
+                           (const uint32_t *)p.sc.keys[src], (const float4 *)p.sc.rec[src ^ 1],
+                           p.sc.keys[src ^ 1], p.sc.rec[src], p.N, shift, (int)p.nblk, pitch,
+                           (const uint32_t *)p.sc.hist,
+                           scan ? (const uint32_t *)p.sc.total : (const uint32_t *)nullptr);
         if ((e = hipGetLastError()) != hipSuccess) return e;
         src ^= 1;
     }
     return hipSuccess;
 }
 
+bool bin_is_small(int64_t max_n, int64_t max_ncell) {
+    return max_n <= kBinSmallN && max_ncell <= kBinSmallCells;
+}
+
+hipError_t bin_small_launch(const Chunk &c, const DevBox *d_boxes, int nbox, hipStream_t s) {
+    hipLaunchKernelGGL(k_bin_small, dim3((unsigned)nbox), dim3(kBinSmallThreads), 0, s, c,
+                       d_boxes);
+    return hipGetLastError();
+}
+
 hipError_t bin_launch(const DevBox *d_boxes, int nbox, const BinPlan &p, hipStream_t s) {
     hipError_t e;
-    hipLaunchKernelGGL(k_bin_zero_status, dim3((nbox + 255) / 256), dim3(256), 0, s, d_boxes, nbox);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
     if (p.N > 0) {
-        hipLaunchKernelGGL(k_bin_keys, dim3((unsigned)((p.max_n + 255) / 256), (unsigned)nbox),
-                           dim3(256), 0, s, d_boxes, p.sc);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-        e = p.radix_bits == 9 ? sort_passes<9>(p, s) : sort_passes<8>(p, s);
+        e = p.radix_bits == 9 ? sort_passes<9>(d_boxes, nbox, p, s)
+                              : sort_passes<8>(d_boxes, nbox, p, s);
         if (e != hipSuccess) return e;
     }
-    // with at least one pass the sorted arrays sit in buffer (passes & 1)
-    const uint32_t *keys = p.sc.keys[p.passes & 1];
-    const uint32_t *vals = p.sc.vals[p.passes & 1];
-    const unsigned first_blocks =
-        (unsigned)std::max<int64_t>(1, std::min<int64_t>(65535, (p.N + 1 + 255) / 256));
-    hipLaunchKernelGGL(k_cell_first, dim3(first_blocks), dim3(256), 0, s, keys, p.N, p.C,
-                       p.sc.cellcnt);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    hipLaunchKernelGGL(k_bin_finish,
-                       dim3((unsigned)((std::max<int64_t>(p.max_n, p.max_ncell + 1) + 255) / 256),
-                            (unsigned)nbox),
-                       dim3(256), 0, s, d_boxes, (const uint32_t *)p.sc.cellcnt, vals,
-                       (const float4 *)p.sc.offc);
+    hipLaunchKernelGGL(k_bin_cells, dim3((unsigned)(p.max_n / 256 + 1), (unsigned)nbox), dim3(256),
+                       0, s, d_boxes, (const uint32_t *)p.sc.keys[p.passes & 1],
+                       (const uint32_t *)p.sc.bad);
     return hipGetLastError();
 }
 

@@ -18,7 +18,6 @@ __device__ __forceinline__ gptr<T> gp(T *p) {
     return (gptr<T>)p;
 }
 
-// Radix sort geometry: 8-bit digits, 256 threads per block, 16 keys per thread.
 // Tile defaults (an nf_box field of 0 picks these).
 constexpr int kDefaultDenseMin = 41;      // nf_box.dense_min
 constexpr int kDefaultNarrowMax = 12;     // nf_box.narrow_max
@@ -29,9 +28,16 @@ constexpr int kDefaultNarrowWindow = 256; // nf_box.narrow_window (128 / 256 / 5
 // pairs, whose force is then min(poly, inf) * 0 = 0, and is far below half an
 // ulp of any separation that floats resolve between offsets of order one.
 constexpr float kR2Floor = 1.0e-30f;
-constexpr int kSortThreads = 256;
-constexpr int kSortItems = 16;
-constexpr int kSortTile = kSortThreads * kSortItems;   // 4096 keys per block
+// Radix sort geometry: 8- or 9-bit digits, 512 threads per block, 4 keys per thread.
+constexpr int kSortThreads = 512;
+constexpr int kSortItems = 4;
+constexpr int kSortTile = kSortThreads * kSortItems;   // 2048 keys per block
+constexpr int kRowTiles = 64;   // up to this many tiles no separate scan of the counts
+// Boxes that one workgroup bins.
+constexpr int kBinSmallThreads = 1024;
+constexpr int kBinSmallItems = 4;
+constexpr int kBinSmallN = kBinSmallThreads * kBinSmallItems;
+constexpr int kBinSmallCells = 65536;
 
 // Scan geometry: 256 threads x 16 items per block.
 constexpr int kScanThreads = 256;
@@ -142,11 +148,11 @@ struct Item {
 // Global (all boxes) scratch used by the binning kernels.
 struct BinScratch {
     uint32_t *keys[2];    // [N] concatenated keys (cellbase_b + cell id)
-    uint32_t *vals[2];    // [N] concatenated element index (vals[0] unused: the
-                          // first pass takes the identity)
-    float4 *offc;         // [N] float offsets and z cell, concatenated caller order
-    uint32_t *hist;       // [radix * nblk] digit-major block histograms
-    uint32_t *cellcnt;    // [C + 1] first sorted slot of each concatenated cell key
+    float4 *rec[2];       // [N] offsets and concatenated index, sorted with the keys
+                          // (rec[0] between passes 1 and 2; rec[1] from three passes on)
+    uint32_t *hist;       // [radix * pitch] digit-major tile histograms
+    uint32_t *total;      // [radix] keys per digit
+    uint32_t *bad;        // [nbox] particles without a cell
 };
 
 // Cell of one coordinate, exactly as the method defines it: s = x * kappa
@@ -154,22 +160,30 @@ struct BinScratch {
 // sequence is evaluated without contraction so that host-side checks can
 // reproduce the rounded offset bit for bit.  Returns false when s is not
 // finite or |s| >= 2^62.
-__device__ __forceinline__ bool cell_coord(double x, double kappa, int K, int &c, double &o) {
+__device__ __forceinline__ bool cell_offset(double x, double kappa, double &f, double &o) {
 #pragma clang fp contract(off)
     double s = x * kappa;
     if (!(fabs(s) < 4.611686018427387904e18)) {   // also catches NaN
-        c = 0;
+        f = 0.0;
         o = 0.0;
         return false;
     }
-    double f = floor(s);
+    f = floor(s);
     double frac = s - f;
     o = frac - 0.5;
-    long long fi = (long long)f;
-    long long r = fi % (long long)K;
-    if (r < 0) r += K;
-    c = (int)r;
     return true;
+}
+__device__ __forceinline__ bool cell_coord(double x, double kappa, int K, int &c, double &o) {
+    double f;
+    const bool ok = cell_offset(x, kappa, f, o);
+    if (f >= 0.0 && f < (double)K) {   // inside the box: no 64-bit remainder
+        c = (int)f;
+    } else {
+        long long r = (long long)f % (long long)K;
+        if (r < 0) r += K;
+        c = (int)r;
+    }
+    return ok;
 }
 
 // Wave-level "match any" on a BITS-bit digit: mask of the active lanes whose

@@ -10,17 +10,23 @@
 
 namespace nf {
 
+// Descriptor bytes travel as a kernel argument (no host-to-device memcpy), so
+// every call is a pure sequence of kernel launches.  3840 bytes and the other
+// arguments fit the 4 KB that kernel arguments may take.
+constexpr int kChunkBytes = 3840;
+struct alignas(8) Chunk {
+    unsigned char bytes[kChunkBytes];
+};
+
 // Sizes and scratch pointers of one binning call (all boxes together).
 struct BinPlan {
     int64_t N = 0;          // sum of n_b
-    int64_t C = 0;          // sum of K_b^3
     int64_t max_n = 0;      // largest n_b
-    int64_t max_ncell = 0;  // largest K_b^3
     int64_t nblk = 0;       // radix tiles: ceil(N / kSortTile)
+    int64_t pitch = 0;      // words per row of the tile histograms
     int passes = 0;         // radix passes covering keys 0..C-1 (at least 1)
     int radix_bits = 8;     // digit width: 8, or 9 when that saves a pass
     BinScratch sc{};
-    uint32_t *scan_scratch = nullptr;
 };
 
 int64_t scan_scratch_words(int64_t M);
@@ -28,7 +34,11 @@ int64_t scan_scratch_words(int64_t M);
 hipError_t scan_exclusive(uint32_t *data, int64_t M, uint32_t *scratch, hipStream_t s);
 // Fill count uint32 values (a kernel, so it can sit inside a captured graph).
 hipError_t fill_u32(uint32_t *p, int64_t count, uint32_t value, hipStream_t s);
+// The counts of bad particles (p.sc.bad) are zeroed by the descriptor upload.
 hipError_t bin_launch(const DevBox *d_boxes, int nbox, const BinPlan &p, hipStream_t s);
+// Boxes that one workgroup bins; their descriptors in c, or at d_boxes.
+bool bin_is_small(int64_t max_n, int64_t max_ncell);
+hipError_t bin_small_launch(const Chunk &c, const DevBox *d_boxes, int nbox, hipStream_t s);
 
 // Pair symmetry (nf_pair.hip).
 struct F4Plan {

@@ -110,6 +110,36 @@ def test_bin_digit_widths(K, n):
     _bin_check(pos, K, L)
 
 
+@pytest.mark.parametrize("Ks,ns", [
+    ([5], [1]), ([7], [1024]), ([16], [1025]), ([17], [4096]), ([40], [3]), ([41], [3]),
+    ([9], [4097]), ([13], [64 * 2048]), ([13], [64 * 2048 + 1]), ([70], [5000]),
+    ([5, 6, 8], [0, 4096, 77]), ([5 + i % 4 for i in range(21)], [40 * i for i in range(21)]),
+    ([8, 5, 30, 6, 7], [2047, 0, 5000, 1, 2050])],
+    ids=lambda v: "-".join(map(str, v[:5])))
+def test_bin_routes_bit_exact(Ks, ns):
+    """Boxes binned by one workgroup (up to 4096 particles and 65536 cells, the
+    descriptors as an argument or, above 20 boxes, from memory) and by the tiled
+    sort (one to three passes, tiles of 2048 that straddle boxes, 64 and 65 of
+    them), with long runs of empty cells and a particle without a cell."""
+    poss, bads = [], []
+    for b, n in enumerate(ns):
+        pos = np.random.default_rng(50 + b).uniform(-0.2, 1.3, size=(n, 3)) ** 3
+        if n > 70:
+            pos[n // 2, b % 3] = np.nan if b % 2 else np.inf
+        poss.append(pos)
+        bads.append(int(n > 70))
+    got = nfp.bin_particles_batched([_gpu(p) for p in poss], Ks, [1.0] * len(Ks),
+                                    [0.01] * len(Ks), check=False)
+    assert got.nbad() == bads
+    for p, K, bx in zip(poss, Ks, got.boxes):
+        bad = ~np.isfinite(p).all(axis=1)
+        cs, order, off = oracle.bin_particles(np.where(bad[:, None], 0.5 / K, p), K, 1.0)
+        off[bad[order]] = 0.0                       # cell 0, offset 0
+        np.testing.assert_array_equal(bx.cell_start.cpu().numpy(), cs)
+        np.testing.assert_array_equal(bx.order.cpu().numpy(), order)
+        assert bx.off.cpu().numpy().tobytes() == off.tobytes()
+
+
 def test_bin_batched_matches_single():
     specs = batched_specs(4, seed=5, lo=4000, hi=9000)
     poss = [make_box(s) for s in specs]
