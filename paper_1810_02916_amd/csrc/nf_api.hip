@@ -44,6 +44,16 @@ hipError_t upload(const void *src, size_t nbytes, void *dst, hipStream_t s,
     return hipSuccess;
 }
 
+// Two tables, the first one's place before the second's, at their offsets in w.
+hipError_t upload_pair(const void *a, size_t na, size_t a_off, const void *b, size_t nb,
+                       size_t b_off, char *w, hipStream_t s, uint32_t *zero = nullptr,
+                       int nzero = 0) {
+    std::vector<char> both(b_off - a_off + nb, 0);
+    std::memcpy(both.data(), a, na);
+    std::memcpy(both.data() + (b_off - a_off), b, nb);
+    return upload(both.data(), both.size(), w + a_off, s, zero, nzero);
+}
+
 size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
 
@@ -89,7 +99,7 @@ struct Layout {
            light_off = 0, counter_off = 0;
     size_t stepio_off = 0, cellstat_off = 0, partial_off = 0, partstat_off = 0;
     size_t mp_base_off = 0, mp_first_off = 0, mp_first_bytes = 0;
-    size_t mp_npieces_off = 0, mp_scan_off = 0, mp_pieces_off = 0, mp_partial_off = 0;
+    size_t mp_total_off = 0, mp_pieces_off = 0, mp_partial_off = 0;
     int64_t mp_max_pieces = 0;
     int64_t max_dense = 0;
     size_t accel_end = 0;   // bytes an accelerations call uses (table + planner)
@@ -255,12 +265,10 @@ int validate(int nbox, const nf_box *boxes, Layout &L, uint32_t flags = 0) {
         nranges += multipole_ranges(boxes[b].n, (int64_t)boxes[b].K * boxes[b].K * boxes[b].K) + 1;
     L.mp_first_bytes = 4 * (size_t)nranges;
     o = align_up(o + L.mp_first_bytes, 256);
-    // cells cut into pieces: counts then offsets, scan scratch, pieces, and
-    // the pieces' double moments at the largest order
-    L.mp_npieces_off = o;
-    o = align_up(o + 4 * (size_t)(L.C + 1), 256);
-    L.mp_scan_off = o;
-    o = align_up(o + 4 * (size_t)scan_scratch_words(L.C + 1), 256);
+    // cells cut into pieces: their count, the pieces, and their double moments
+    // at the largest order
+    L.mp_total_off = o;
+    o = align_up(o + 4, 256);
     for (int b = 0; b < nbox; ++b) L.mp_max_pieces += multipole_max_pieces(boxes[b].n);
     L.mp_pieces_off = o;
     o = align_up(o + sizeof(MpPiece) * (size_t)L.mp_max_pieces, 256);
@@ -776,18 +784,17 @@ int nf_multipoles(int nbox, const nf_box *boxes, int order, float *const *mom, v
         DevBox *d_tab = reinterpret_cast<DevBox *>(w + L.table_off);
         int64_t *d_rbase = reinterpret_cast<int64_t *>(w + L.mp_base_off);
         MpPlan mp;
-        mp.C = L.C;
         mp.max_ncell = L.max_ncell;
         mp.max_ranges = max_ranges;
         mp.max_pieces = L.mp_max_pieces;
         mp.range_base = d_rbase;
         mp.first = reinterpret_cast<int32_t *>(w + L.mp_first_off);
-        mp.npieces = reinterpret_cast<uint32_t *>(w + L.mp_npieces_off);
-        mp.scan = reinterpret_cast<uint32_t *>(w + L.mp_scan_off);
+        mp.total = reinterpret_cast<uint32_t *>(w + L.mp_total_off);
         mp.pieces = reinterpret_cast<MpPiece *>(w + L.mp_pieces_off);
         mp.partial = reinterpret_cast<double *>(w + L.mp_partial_off);
-        hipError_t e = upload(tab.data(), sizeof(DevBox) * tab.size(), d_tab, s);
-        if (e == hipSuccess) e = upload(rbase.data(), sizeof(int64_t) * rbase.size(), d_rbase, s);
+        hipError_t e = upload_pair(tab.data(), sizeof(DevBox) * tab.size(), L.table_off,
+                                   rbase.data(), sizeof(int64_t) * rbase.size(), L.mp_base_off, w,
+                                   s, mp.total, 1);
         if (e == hipSuccess) e = multipole_launch(d_tab, nbox, mp, order, s);
         if (e != hipSuccess) return fail(NF_EHIP, std::string("multipoles: ") + hipGetErrorString(e));
         g_last_error.clear();

@@ -107,14 +107,12 @@ struct MpPiece {
     int32_t box, cell, q0, q1, k, np;   // sorted slots [q0, q1); piece k of np
 };
 struct MpPlan {
-    int64_t C = 0;                  // cells over all boxes
     int64_t max_ncell = 0;          // largest per-box cell count
     int64_t max_ranges = 0;         // largest per-box range count
     int64_t max_pieces = 0;         // bound on the pieces over all boxes
     const int64_t *range_base = nullptr;   // [nbox + 1] prefix of the range counts
     int32_t *first = nullptr;       // sum over boxes of (ranges + 1)
-    uint32_t *npieces = nullptr;    // [C + 1] pieces per cell, then their offsets
-    uint32_t *scan = nullptr;       // scan_scratch_words(C + 1)
+    uint32_t *total = nullptr;      // [1] pieces over all boxes
     MpPiece *pieces = nullptr;      // [max_pieces]
     double *partial = nullptr;      // [max_pieces][terms] piece moments
 };

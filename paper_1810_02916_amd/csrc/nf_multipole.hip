@@ -1,22 +1,31 @@
 // One wave per workgroup.  Lane u owns a unit: a product x^a y^b and up to
 // four consecutive powers z^c0 .. z^(c0+3) of the same (a, b), so its terms
-// x^a y^b z^c share one product, each added by one fused multiply-add with a
-// staged z power (61 units cover the 165 terms of order 8).  Particles are
-// staged 64 at a time as double powers x^k, y^k, z^k in LDS (the next 64
-// offsets are loaded while the current ones are summed).
+// share one product x^a (y^b z^c0), each added by one fused multiply-add with
+// z^0 .. z^3 (61 units cover the 165 terms of order 8).  Particles are staged
+// 64 at a time: double x^k and y^b z^c0 in LDS, one row per power, z in the
+// lane's register (the next 64 offsets are loaded while the current ones are
+// summed).
 //
+//   k_mp_plan     the first cell of every run, and the pieces of the big cells
 //   k_multipoles  a run of consecutive cells of bounded cost (particles plus
 //                 a fixed cost per cell) per workgroup; each lane adds its
-//                 terms over the run's particles in sorted order, one cell
-//                 segment at a time, and writes a cell's moments as it passes
-//                 the cell's end.  Cells of more than kBig particles are
-//                 skipped: one workgroup summing them alone would set the
-//                 kernel's length.
-//   k_mp_pieces   those cells, cut into pieces of kBig particles, one piece
-//                 per workgroup, moments of the piece in double;
+//                 terms over the run's particles in sorted order and writes a
+//                 cell's moments as it passes the cell's end.  Cells of more
+//                 than kBig particles are skipped: one workgroup summing them
+//                 alone would set the kernel's length; their pieces of kBig
+//                 particles, moments in double, are the kernel's first
+//                 workgroups.
 //   k_mp_combine  adds a cell's pieces in piece order and writes its moments.
 // Every moment is a fixed sequence of double operations, so the moments are
 // reproducible.
+//
+// Bound by VALU issue (counted: 16 operations a particle, 9 of them its sums,
+// the rest staging and stores): a particle takes 17 clocks of a CU there and 9
+// of LDS; with the four z powers read from LDS too that was 24 and set the time.
+// 6 KB of LDS a workgroup, so that registers limit the waves (five per SIMD), and
+// short runs, so that the last ones even out.  64^3 cells, 2.1M clustered
+// particles, order 8 (173 MB of moments), the whole call: 151 -> 110 us; 50k
+// particles of 18^3 cells 45 -> 25.
 #include "nf_internal.h"
 #include "nf_kernels.h"
 
@@ -25,21 +34,26 @@ namespace {
 
 constexpr int kMaxOrder = 8;
 constexpr int kUnitTerms = 4;       // consecutive z powers per lane
-constexpr int kChunk = 64;          // particles staged per round (one per lane)
-// staged powers of one particle: x^0..8, y^0..8, then z^0..11 (a unit starting
-// at z^8 reads four; the powers past the order feed terms that are never stored)
-constexpr int kZPow = kMaxOrder + kUnitTerms;
-constexpr int kPow = 2 * (kMaxOrder + 1) + kZPow;
-static_assert(kPow % 2 == 0 && (2 * (kMaxOrder + 1)) % 2 == 0 && kUnitTerms % 2 == 0,
-              "z powers of a unit are read as 16-byte pairs");
+constexpr int kChunk = 32;          // particles staged per round (one per lane)
+// rows of staged powers: x^0..8, then y^b z^c0 for c0 = 0 (b = 0..8), 4 (0..4)
+// and 8 (0); a row holds one double per particle and one of padding, which
+// spreads the rows over the LDS banks
+constexpr int yz_row(int b, int c0) {
+    return kMaxOrder + 1 + b + (c0 >= 4 ? kMaxOrder + 1 : 0) + (c0 >= 8 ? kMaxOrder - 4 + 1 : 0);
+}
+constexpr int kRows = yz_row(0, 8) + 1;
+constexpr int kRowLen = kChunk + 1;
+static_assert(kMaxOrder == 8 && kUnitTerms == 4, "the rows above");
 // Work partition: cell c costs its particles plus kCellCost (its T stores);
 // workgroup w takes the cells whose cumulative cost
 //   cost(c) = cell_start[c] + kCellCost * c
 // lies in [w kRange, (w + 1) kRange).  cost is increasing in c, so the first
 // cell of every range is found by one pass over the cells.
 constexpr int kCellCost = 8;
-constexpr int kRange = 512;
-constexpr int kBig = 512;           // larger cells are summed in pieces of kBig
+constexpr int kRange = 128;
+constexpr int kBatch = 4;           // chunks whose offsets are loaded together: a load waits
+                                    // for the stores before it (they return in order)
+constexpr int kBig = 256;           // larger cells are summed in pieces of kBig
 constexpr int kMaxTerms = (kMaxOrder + 1) * (kMaxOrder + 2) * (kMaxOrder + 3) / 6;
 
 __device__ __forceinline__ int64_t cell_cost(const int32_t *cs, int c) {
@@ -54,10 +68,13 @@ constexpr int term_index(int a, int b, int c) {
 }
 
 // first[w] = smallest c with cost(c) >= w kRange, for w = 0 .. nrange - 1,
-// and first[nrange] = ncell.
+// and first[nrange] = ncell.  The pieces of each cell of more than kBig
+// particles, in order from wherever the count of pieces stands (total, zeroed
+// by the descriptor upload): no moment depends on the place.
 __global__ void __launch_bounds__(256)
-k_mp_ranges(const DevBox *__restrict__ boxes, const int64_t *__restrict__ range_base,
-            int32_t *__restrict__ first) {
+k_mp_plan(const DevBox *__restrict__ boxes, const int64_t *__restrict__ range_base,
+          int32_t *__restrict__ first, uint32_t *__restrict__ total,
+          MpPiece *__restrict__ pieces, int64_t max_pieces) {
     const DevBox &B = boxes[blockIdx.y];
     int32_t *f = first + range_base[blockIdx.y] + blockIdx.y;   // nrange + 1 entries per box
     const int nrange = (int)(range_base[blockIdx.y + 1] - range_base[blockIdx.y]);
@@ -66,22 +83,30 @@ k_mp_ranges(const DevBox *__restrict__ boxes, const int64_t *__restrict__ range_
     if (c == 0) {
         f[0] = 0;
         f[nrange] = B.ncell;
-        return;
+    } else {
+        const int64_t lo = cell_cost(B.cell_start, c - 1) / kRange + 1;
+        const int64_t hi = cell_cost(B.cell_start, c) / kRange;
+        for (int64_t w = lo; w <= hi && w < nrange; ++w) f[w] = c;
     }
-    const int64_t lo = cell_cost(B.cell_start, c - 1) / kRange + 1;
-    const int64_t hi = cell_cost(B.cell_start, c) / kRange;
-    for (int64_t w = lo; w <= hi && w < nrange; ++w) f[w] = c;
+    if (c == B.ncell) return;
+    const int q = B.cell_start[c], n = B.cell_start[c + 1] - q;
+    if (n <= kBig) return;
+    const int np = (n + kBig - 1) / kBig;
+    const int64_t at = atomicAdd(total, (uint32_t)np);
+    for (int k = 0; k < np && at + k < max_pieces; ++k)
+        pieces[at + k] = MpPiece{(int32_t)blockIdx.y, c, q + k * kBig, min(q + n, q + (k + 1) * kBig),
+                                 k, np};
 }
 
 // The lanes' units for every order p: (a, b) pairs in order, each cut into
-// runs of <= 4 z powers of which the first uk are terms.  ia, ib, ic index a
-// particle's staged powers; idx are the storage indices of the unit's terms,
+// runs of <= 4 z powers of which the first uk are terms.  ia and iyz are the rows
+// of their staged powers; idx are the storage indices of the unit's terms,
 // and for j >= uk idx[j] repeats idx[0], so that a lane stores all four slots
 // without a branch (the extra stores rewrite term 0 with its own value).
 // Lanes without a unit repeat lane 0's: they compute and store the same
 // values at the same places.  Built at compile time, read once per workgroup.
 struct LaneUnit {
-    int16_t ia, ib, ic, uk;
+    int16_t ia, iyz, uk;
     int16_t idx[kUnitTerms];
 };
 struct UnitTable {
@@ -94,8 +119,7 @@ constexpr UnitTable make_units() {
         for (int a = 0; a <= p; ++a)
             for (int b = 0; a + b <= p; ++b)
                 for (int c = 0; a + b + c <= p; c += kUnitTerms, ++n) {
-                    LaneUnit L{(int16_t)a, (int16_t)(kMaxOrder + 1 + b),
-                               (int16_t)(2 * (kMaxOrder + 1) + c),
+                    LaneUnit L{(int16_t)a, (int16_t)yz_row(b, c),
                                (int16_t)(p - a - b - c + 1 < kUnitTerms ? p - a - b - c + 1
                                                                         : kUnitTerms),
                                {0, 0, 0, 0}};
@@ -119,45 +143,66 @@ __constant__ UnitTable kUnits = make_units();
 
 __device__ __forceinline__ LaneUnit lane_unit(int p, int t) { return kUnits.u[p][t]; }
 
-// Lane t < cnt writes the powers 0..p of x and y and 0..11 of z of its
-// particle's offset o.
-__device__ __forceinline__ void stage_powers(double (*pw)[kPow], int t, int cnt, int p, float4 o) {
+// Lane t < cnt writes the powers of its particle's offset o, up to the largest
+// order: straight-line code, cheaper than a loop to the call's order.
+__device__ __forceinline__ void stage_powers(double (*pw)[kRowLen], int t, int cnt, float4 o) {
     if (t < cnt) {
-        const double x = o.x, y = o.y, z = o.z;
+        const double x = o.x, y = o.y, z = o.z, z2 = z * z, z4 = z2 * z2;
         double px = 1.0, py = 1.0;
-        for (int k = 0; k <= p; ++k) {
-            pw[t][k] = px;
-            pw[t][kMaxOrder + 1 + k] = py;
+#pragma unroll
+        for (int k = 0; k <= kMaxOrder; ++k) {
+            pw[k][t] = px;
+            pw[yz_row(k, 0)][t] = py;
+            if (k + 4 <= kMaxOrder) pw[yz_row(k, 4)][t] = py * z4;
             px *= x;
             py *= y;
         }
-        double pz = 1.0;
-#pragma unroll
-        for (int k = 0; k < kZPow; ++k) {
-            pw[t][2 * (kMaxOrder + 1) + k] = pz;
-            pz *= z;
-        }
+        pw[yz_row(0, 8)][t] = z4 * z4;
     }
 }
 
-// acc[j] += sum over staged particles l in [l0, l1), in order, of
-// x^a y^b z^(c0 + j), each term one fused multiply-add of the product
-// x^a y^b and the staged z power.  Terms past the unit's last one are computed
-// and never stored.
-__device__ __forceinline__ void add_staged(const double (*pw)[kPow], int l0, int l1,
-                                           const LaneUnit &U, double acc[kUnitTerms]) {
-    // unrolled so that the loads and products of several particles are in
-    // flight at once; only the additions into acc chain
-#pragma unroll 4
-    for (int l = l0; l < l1; ++l) {
-        const double m = pw[l][U.ia] * pw[l][U.ib];
-        // z^c0 .. z^(c0+3): c0 is a multiple of 4 and rows are 16-byte multiples
-        const double2 z01 = *reinterpret_cast<const double2 *>(&pw[l][U.ic]);
-        const double2 z23 = *reinterpret_cast<const double2 *>(&pw[l][U.ic + 2]);
-        acc[0] = __builtin_fma(m, z01.x, acc[0]);
-        acc[1] = __builtin_fma(m, z01.y, acc[1]);
-        acc[2] = __builtin_fma(m, z23.x, acc[2]);
-        acc[3] = __builtin_fma(m, z23.y, acc[3]);
+// acc[j] += sum over the cnt staged particles, in order, of x^a y^b z^(c0 + j);
+// z: lane l's is particle l's.  at(l) runs before particle l is added.  The
+// powers of the next four particles are read while four are added, also
+// across at().  Terms past the unit's last one are computed and never stored.
+template <class At>
+__device__ __forceinline__ void add_staged(const double (*pw)[kRowLen], int cnt, float z,
+                                           const LaneUnit &U, double (&acc)[kUnitTerms], At at) {
+    constexpr int kAhead = 4;
+    static_assert(kChunk % kAhead == 0, "whole groups");
+    const double *xa = pw[U.ia], *yz = pw[U.iyz];
+    double x[kAhead], w[kAhead];
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) {
+        x[u] = xa[u];
+        w[u] = yz[u];
+    }
+    for (int l0 = 0; l0 < cnt; l0 += kAhead) {
+        double m[kAhead];
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) m[u] = x[u] * w[u];
+        const int next = l0 + kAhead < cnt ? l0 + kAhead : l0;
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+            x[u] = xa[next + u];
+            w[u] = yz[next + u];
+        }
+        double z1[kAhead], z2[kAhead], z3[kAhead];
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+            z1[u] = (double)__int_as_float(__builtin_amdgcn_readlane(__float_as_int(z), l0 + u));
+            z2[u] = z1[u] * z1[u];
+            z3[u] = z2[u] * z1[u];
+        }
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+            if (l0 + u >= cnt) break;
+            at(l0 + u);
+            acc[0] += m[u];
+            acc[1] = __builtin_fma(m[u], z1[u], acc[1]);
+            acc[2] = __builtin_fma(m[u], z2[u], acc[2]);
+            acc[3] = __builtin_fma(m[u], z3[u], acc[3]);
+        }
     }
 }
 
@@ -167,12 +212,47 @@ __device__ __forceinline__ float4 ld_off(gptr<const float> off, int i) {
     return make_float4(q[0], q[1], q[2], 0.f);
 }
 
+// The moments of piece w of a big cell, in double.
+__device__ __forceinline__ void piece_moments(const DevBox *__restrict__ boxes, const MpPiece &pc,
+                                              double *__restrict__ partial, int p,
+                                              double (*pw)[kRowLen]) {
+    const int t = threadIdx.x;
+    const LaneUnit U = lane_unit(p, t);
+    const gptr<const float> off = gp((const float *)boxes[pc.box].off);
+    double acc[kUnitTerms] = {0.0, 0.0, 0.0, 0.0};
+    float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (pc.q0 + t < pc.q1) o = ld_off(off, pc.q0 + t);
+    for (int s = pc.q0; s < pc.q1; s += kChunk) {
+        const int e = min(s + kChunk, pc.q1);
+        __syncthreads();
+        stage_powers(pw, t, e - s, o);
+        const float z = o.z;
+        if (e + t < pc.q1) o = ld_off(off, e + t);
+        __syncthreads();
+        add_staged(pw, e - s, z, U, acc, [](int) {});
+    }
+#pragma unroll
+    for (int j = 0; j < kUnitTerms; ++j) gp(partial)[U.idx[j]] = j < U.uk ? acc[j] : acc[0];
+}
+
+// Workgroup (x, y): piece y * npiece_blocks + x for x < npiece_blocks (the pieces
+// of all boxes; most grids have more such workgroups than pieces, and these end
+// at once), else run x - npiece_blocks of box y.
 __global__ void __launch_bounds__(64)
 k_multipoles(const DevBox *__restrict__ boxes, const int64_t *__restrict__ range_base,
-             const int32_t *__restrict__ first, int p, int nterms) {
-    __shared__ __align__(16) double pw[kChunk][kPow];   // powers of the staged particles
+             const int32_t *__restrict__ first, int p, int nterms, int npiece_blocks,
+             const MpPiece *__restrict__ pieces, const uint32_t *__restrict__ total,
+             int64_t max_pieces, double *__restrict__ partial) {
+    __shared__ __align__(16) double pw[kRows][kRowLen];   // powers of the staged particles
+    static_assert(kChunk == 32, "one staged particle per lane");
     const int box = blockIdx.y;
-    const int w = blockIdx.x;
+    if ((int)blockIdx.x < npiece_blocks) {
+        const int64_t i = (int64_t)box * npiece_blocks + blockIdx.x;
+        if (i < min((int64_t)*total, max_pieces))
+            piece_moments(boxes, pieces[i], partial + i * kMaxTerms, p, pw);
+        return;
+    }
+    const int w = (int)blockIdx.x - npiece_blocks;
     if ((int64_t)w >= range_base[box + 1] - range_base[box]) return;   // whole workgroup
     const DevBox &B = boxes[box];
     const int32_t *f = first + range_base[box] + box;
@@ -182,7 +262,6 @@ k_multipoles(const DevBox *__restrict__ boxes, const int64_t *__restrict__ range
     const gptr<const float> off = gp((const float *)B.off);
     const gptr<float> out = gp(B.out);
     static_assert(kRange % kCellCost == 0, "range bound");
-    static_assert(kChunk <= 64, "one staged particle per lane");
     const int c0 = f[w], c1 = f[w + 1];
     if (c0 >= c1) return;
     // each cell costs >= kCellCost, so a range holds at most kRange / kCellCost
@@ -194,12 +273,16 @@ k_multipoles(const DevBox *__restrict__ boxes, const int64_t *__restrict__ range
     auto cbeg = [&](int cell) { return __builtin_amdgcn_readlane(cbeg_l, cell - c0); };
     auto cend_of = [&](int cell) { return __builtin_amdgcn_readlane(cend_l, cell - c0); };
     double acc[kUnitTerms] = {0.0, 0.0, 0.0, 0.0};
+    uint32_t at_byte[kUnitTerms];
+#pragma unroll
+    for (int j = 0; j < kUnitTerms; ++j) at_byte[j] = 4u * (uint32_t)U.idx[j];
     auto flush = [&](int cell) {
-        const gptr<float> o = out + (int64_t)cell * nterms;
+        // (scalar base, 32-bit byte offsets)
+        const gptr<char> o = (gptr<char>)(out + (int64_t)cell * nterms);
         const float v0 = (float)acc[0];
 #pragma unroll
         for (int j = 0; j < kUnitTerms; ++j) {
-            o[U.idx[j]] = j < U.uk ? (float)acc[j] : v0;
+            *(gptr<float>)(o + at_byte[j]) = j < U.uk ? (float)acc[j] : v0;
             acc[j] = 0.0;
         }
     };
@@ -214,83 +297,30 @@ k_multipoles(const DevBox *__restrict__ boxes, const int64_t *__restrict__ range
         const int p0 = cbeg(ca), p1 = cend_of(cb - 1);
         int cell = ca;
         int cend = cend_of(ca);
-        float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (t < kChunk && p0 + t < p1) o = ld_off(off, p0 + t);
-        for (int s = p0; s < p1; s += kChunk) {
+        float4 o[kBatch];
+        for (int s = p0, q = 0; s < p1; s += kChunk, q = (q + 1) % kBatch) {
             const int e = min(s + kChunk, p1);
+            if (q == 0) {
+#pragma unroll
+                for (int k = 0; k < kBatch; ++k) o[k] = ld_off(off, min(s + k * kChunk + t, p1 - 1));
+            }
             __syncthreads();   // the previous chunk is consumed
-            stage_powers(pw, t, e - s, p, o);
-            if (t < kChunk && e + t < p1) o = ld_off(off, e + t);   // next chunk, in flight
+            stage_powers(pw, t, e - s, o[0]);
+            const float z = o[0].z;
+#pragma unroll
+            for (int k = 0; k + 1 < kBatch; ++k) o[k] = o[k + 1];
             __syncthreads();
-            for (int i = s; i < e;) {   // segments of the chunk that lie in one cell
-                while (i >= cend) {     // cells that end at or before particle i
+            add_staged(pw, e - s, z, U, acc, [&](int l) {
+                while (s + l >= cend) {   // cells that end at or before the particle
                     flush(cell);
                     ++cell;
                     cend = cend_of(cell);
                 }
-                const int j = min(e, cend);
-                add_staged(pw, i - s, j - s, U, acc);
-                i = j;
-            }
+            });
         }
         for (; cell < cb; ++cell) flush(cell);   // the run's last cells (and empty ones)
         ca = cb;
     }
-}
-
-// Pieces per cell (0 for a cell of at most kBig particles).
-__global__ void __launch_bounds__(256)
-k_mp_count(const DevBox *__restrict__ boxes, uint32_t *__restrict__ npieces) {
-    const DevBox &B = boxes[blockIdx.y];
-    const int c = blockIdx.x * 256 + threadIdx.x;
-    if (c >= B.ncell) return;
-    const gptr<const int32_t> cs = gp(B.cell_start);
-    const int n = cs[c + 1] - cs[c];
-    npieces[B.cellbase + c] = n > kBig ? (uint32_t)((n + kBig - 1) / kBig) : 0u;
-}
-
-// The pieces of each big cell at its offset (the exclusive scan of the counts).
-__global__ void __launch_bounds__(256)
-k_mp_emit(const DevBox *__restrict__ boxes, const uint32_t *__restrict__ offsets,
-          MpPiece *__restrict__ pieces, int64_t max_pieces) {
-    const DevBox &B = boxes[blockIdx.y];
-    const int c = blockIdx.x * 256 + threadIdx.x;
-    if (c >= B.ncell) return;
-    const gptr<const int32_t> cs = gp(B.cell_start);
-    const int q = cs[c], n = cs[c + 1] - q;
-    if (n <= kBig) return;
-    const int np = (n + kBig - 1) / kBig;
-    const int64_t at = offsets[B.cellbase + c];
-    for (int k = 0; k < np && at + k < max_pieces; ++k)
-        pieces[at + k] = MpPiece{(int32_t)blockIdx.y, c, q + k * kBig, min(q + n, q + (k + 1) * kBig),
-                                 k, np};
-}
-
-__global__ void __launch_bounds__(64)
-k_mp_pieces(const DevBox *__restrict__ boxes, const MpPiece *__restrict__ pieces,
-            const uint32_t *__restrict__ total, double *__restrict__ partial, int p) {
-    __shared__ __align__(16) double pw[kChunk][kPow];
-    const int w = blockIdx.x;
-    if (w >= (int64_t)*total) return;   // whole workgroup
-    const MpPiece pc = pieces[w];
-    const DevBox &B = boxes[pc.box];
-    const int t = threadIdx.x;
-    const LaneUnit U = lane_unit(p, t);
-    const gptr<const float> off = gp((const float *)B.off);
-    double acc[kUnitTerms] = {0.0, 0.0, 0.0, 0.0};
-    float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (t < kChunk && pc.q0 + t < pc.q1) o = ld_off(off, pc.q0 + t);
-    for (int s = pc.q0; s < pc.q1; s += kChunk) {
-        const int e = min(s + kChunk, pc.q1);
-        __syncthreads();
-        stage_powers(pw, t, e - s, p, o);
-        if (t < kChunk && e + t < pc.q1) o = ld_off(off, e + t);
-        __syncthreads();
-        add_staged(pw, 0, e - s, U, acc);
-    }
-#pragma unroll
-    for (int j = 0; j < kUnitTerms; ++j)
-        partial[(int64_t)w * kMaxTerms + U.idx[j]] = j < U.uk ? acc[j] : acc[0];
 }
 
 // The first piece of each big cell adds the cell's pieces in order.
@@ -328,30 +358,20 @@ int64_t multipole_max_pieces(int64_t n) { return 2 * (n / kBig) + 1; }
 
 hipError_t multipole_launch(const DevBox *d_boxes, int nbox, const MpPlan &mp, int p,
                             hipStream_t s) {
-    const dim3 cells((unsigned)((mp.max_ncell + 255) / 256), (unsigned)nbox);
-    hipLaunchKernelGGL(k_mp_ranges, dim3((unsigned)((mp.max_ncell + 1 + 255) / 256), (unsigned)nbox),
-                       dim3(256), 0, s, d_boxes, mp.range_base, mp.first);
+    hipLaunchKernelGGL(k_mp_plan, dim3((unsigned)((mp.max_ncell + 1 + 255) / 256), (unsigned)nbox),
+                       dim3(256), 0, s, d_boxes, mp.range_base, mp.first, mp.total, mp.pieces,
+                       mp.max_pieces);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    // big cells: counts, offsets (the last entry becomes the total), pieces
-    if ((e = fill_u32(mp.npieces, mp.C + 1, 0u, s)) != hipSuccess) return e;
-    hipLaunchKernelGGL(k_mp_count, cells, dim3(256), 0, s, d_boxes, mp.npieces);
+    const unsigned piece_blocks = (unsigned)((mp.max_pieces + nbox - 1) / nbox);
+    hipLaunchKernelGGL(k_multipoles, dim3((unsigned)mp.max_ranges + piece_blocks, (unsigned)nbox),
+                       dim3(64), 0, s, d_boxes, mp.range_base, (const int32_t *)mp.first, p,
+                       multipole_terms(p), (int)piece_blocks, (const MpPiece *)mp.pieces,
+                       (const uint32_t *)mp.total, mp.max_pieces, mp.partial);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    if ((e = scan_exclusive(mp.npieces, mp.C + 1, mp.scan, s)) != hipSuccess) return e;
-    hipLaunchKernelGGL(k_mp_emit, cells, dim3(256), 0, s, d_boxes,
-                       (const uint32_t *)mp.npieces, mp.pieces, mp.max_pieces);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    hipLaunchKernelGGL(k_multipoles, dim3((unsigned)mp.max_ranges, (unsigned)nbox), dim3(64), 0, s,
-                       d_boxes, mp.range_base, (const int32_t *)mp.first, p, multipole_terms(p));
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    const uint32_t *total = mp.npieces + mp.C;
-    const unsigned gp = (unsigned)std::max<int64_t>(1, mp.max_pieces);
-    hipLaunchKernelGGL(k_mp_pieces, dim3(gp), dim3(64), 0, s, d_boxes,
-                       (const MpPiece *)mp.pieces, total, mp.partial, p);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    hipLaunchKernelGGL(k_mp_combine, dim3(gp), dim3(64), 0, s, d_boxes,
-                       (const MpPiece *)mp.pieces, total, (const double *)mp.partial,
-                       multipole_terms(p));
+    hipLaunchKernelGGL(k_mp_combine, dim3((unsigned)std::max<int64_t>(1, mp.max_pieces)), dim3(64),
+                       0, s, d_boxes, (const MpPiece *)mp.pieces, (const uint32_t *)mp.total,
+                       (const double *)mp.partial, multipole_terms(p));
     return hipGetLastError();
 }
 

@@ -95,3 +95,18 @@ def test_multipoles_big_cells_in_pieces(p):
         g = g.cpu().numpy().astype(np.float64)
         np.testing.assert_array_equal(g[:, 0], ref[:, 0])
         assert (np.abs(g - ref32) <= tol).all()
+
+
+@pytest.mark.parametrize("p", [2, 3, 5, 8])
+def test_multipoles_cells_around_chunk_run_and_piece_sizes(p):
+    """Cell counts around a staged chunk (32), a group of four, and a piece
+    (256), between runs of empty cells, and a box without particles."""
+    K, L = 6, 1.0
+    counts = [0, 1, 3, 4, 5, 0, 0, 31, 32, 33, 63, 65, 0, 255, 256, 257, 0, 511, 512, 513]
+    rng = np.random.default_rng(81)
+    parts = [(np.array([c // 36, c // 6 % 6, c % 6]) + rng.uniform(0, 1, (counts[c % 20], 3))) / K
+             for c in range(60)]
+    pos = np.concatenate(parts)
+    _check(pos[rng.permutation(len(pos))], K, L, p)
+    empty = nfp.bin_particles(torch.empty((0, 3), dtype=torch.float64, device=DEV), K, L, 0.01)
+    assert (nfp.multipoles(empty, p) == 0).all()
