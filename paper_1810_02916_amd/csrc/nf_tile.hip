@@ -188,6 +188,22 @@ k_plan_count(const DevBox *boxes, uint32_t *cellinfo, uint32_t *bucket_cnt, int 
         if (h[t]) atomicAdd(&bucket_cnt[t], h[t]);
 }
 
+// Heavy dense items, the first of the list: those of more than 1 / share of all
+// dense items' sources, which one wave each would still be summing when the rest
+// of the call is done.  A lane's buckets b0 and b0 - 1 hold c0 and c1 items.
+// Shares measured at 262k particles, us: accelerations 500 / 1000 / 2000: 340 /
+// 264 / 331; VJP 1000 / 1400 / 2000 / 4000: 473 / 412 / 436 / 463.
+constexpr float kHeavyShareAccel = 1000.0f, kHeavyShareVjp = 1400.0f;
+__device__ __forceinline__ uint32_t heavy_items(int b0, int c0, int c1, float share) {
+    const float s0 = exp2f(0.25f * (float)b0), s1 = exp2f(0.25f * (float)(b0 - 1));
+    float all = (float)c0 * s0 + (float)c1 * s1;
+    for (int o = 32; o >= 1; o >>= 1) all += __shfl_xor(all, o, 64);
+    const float least = all / share;
+    uint32_t n = (s0 > least ? (uint32_t)c0 : 0u) + (s1 > least ? (uint32_t)c1 : 0u);
+    for (int o = 32; o >= 1; o >>= 1) n += __shfl_xor(n, o, 64);
+    return n;
+}
+
 // Items into their bucket ranges: each block adds up the bucket counts of all
 // blocks (highest bucket first), reserves one range per non-empty bucket with a
 // global atomic and places its cells by LDS ranks.  The order inside a bucket
@@ -196,7 +212,7 @@ k_plan_count(const DevBox *boxes, uint32_t *cellinfo, uint32_t *bucket_cnt, int 
 __global__ void __launch_bounds__(256)
 k_plan_emit(const DevBox *boxes, const uint32_t *__restrict__ cellinfo,
             const uint32_t *__restrict__ bucket_cnt, uint32_t *bucket_cur, uint32_t *totals,
-            Item *dense, Item *light) {
+            Item *dense, Item *light, float heavy_share) {
     __shared__ uint32_t h[kKinds * kBuckets];
     __shared__ uint32_t base[kKinds * kBuckets];
     __shared__ uint32_t tot[kKinds];
@@ -211,6 +227,10 @@ k_plan_emit(const DevBox *boxes, const uint32_t *__restrict__ cellinfo,
         if (lane == 63) {
             tot[wave] = (uint32_t)x;
             if (blockIdx.x == 0 && blockIdx.y == 0) totals[wave] = (uint32_t)x;
+        }
+        if (wave == 0 && blockIdx.x == 0 && blockIdx.y == 0) {
+            const uint32_t heavy = heavy_items(b0, c0, c1, heavy_share);
+            if (lane == 0) totals[3] = heavy;
         }
     }
     for (int t = threadIdx.x; t < kKinds * kBuckets; t += 256) h[t] = 0;
@@ -610,14 +630,12 @@ __device__ __forceinline__ void run_scalar(cfloat *__restrict__ src, int j0, int
     }
 }
 
+// Dense items by one wave each, drawn from the queues at counter.
 template <int MODE, bool COMP>
-__global__ void __launch_bounds__(kUnit)
-k_dense(const DevBox *__restrict__ boxes, const Item *__restrict__ items,
-        const uint32_t *__restrict__ totals, uint32_t *counter,
-        const float4 *__restrict__ cot_sorted) {
-    __shared__ int s_item;
-    const int lane = threadIdx.x;
-    const int nitems = (int)totals[0];
+__device__ __forceinline__ void dense_items(const int lane, const DevBox *__restrict__ boxes,
+                                            const Item *__restrict__ items, int nitems,
+                                            uint32_t *counter,
+                                            const float4 *__restrict__ cot_sorted) {
     // one queue per XCD (workgroup w runs on XCD w % 8): XCD x takes the
     // blocks of up to kDenseBlock consecutive items c = x, x + 8, ... in order, so
     // the chunks of one cell, which share every source, meet in one L2, and
@@ -627,14 +645,11 @@ k_dense(const DevBox *__restrict__ boxes, const Item *__restrict__ items,
     const int xb = xcd_block_log2(nitems, kDenseBlock);
     uint32_t *dq = counter + kQueueStride * x;
     for (;;) {
-        if (lane == 0) {
-            const int t = (int)__hip_atomic_fetch_add(gp(dq), 1u, __ATOMIC_RELAXED,
-                                                      __HIP_MEMORY_SCOPE_AGENT);
-            s_item = xcd_item(t, x, xb);
-        }
-        __syncthreads();
-        const int itx = uni(s_item);
-        __syncthreads();
+        int t = 0;
+        if (lane == 0)
+            t = (int)__hip_atomic_fetch_add(gp(dq), 1u, __ATOMIC_RELAXED,
+                                            __HIP_MEMORY_SCOPE_AGENT);
+        const int itx = xcd_item(uni(t), x, xb);
         if (itx >= nitems) break;
         const gptr<const Item> ip = gp(items) + itx;
         const Item I{ip->box, ip->cell0, ip->m, ip->chunk};
@@ -722,6 +737,14 @@ k_dense(const DevBox *__restrict__ boxes, const Item *__restrict__ items,
     }
 }
 
+template <int MODE, bool COMP>
+__global__ void __launch_bounds__(kUnit)
+k_dense(const DevBox *__restrict__ boxes, const Item *__restrict__ items,
+        const uint32_t *__restrict__ totals, uint32_t *counter,
+        const float4 *__restrict__ cot_sorted) {
+    dense_items<MODE, COMP>((int)threadIdx.x, boxes, items, (int)totals[0], counter, cot_sorted);
+}
+
 // ------------------------------------------------------------------ dense path, few items
 
 // A dense item by a whole workgroup, for calls with too few dense items to fill
@@ -735,25 +758,31 @@ k_dense(const DevBox *__restrict__ boxes, const Item *__restrict__ items,
 // them in order, each pair one fused multiply-add with the operands, the order
 // and the compensated folds of k_dense, so the sums are the same bit for bit.
 // Producers work one round of P groups ahead of the consumers, in two
-// buffers, with one barrier per round.  LDS traffic (10 KB per 256 pairs) makes
-// a pair dearer than k_dense's once the card is full: see kWideMaxAccel.  P
-// producers: k_dense_wide five (three workgroups a CU), k_small thirteen.
+// buffers, with one barrier per round.  A pair costs more than k_dense's (10 KB of
+// LDS traffic and the consumers' operations per 256 pairs), so k_dense_wide (five
+// producers, three workgroups a CU) takes only the heavy items this way and the
+// rest a wave each; k_small (thirteen producers, one workgroup a CU) all of them.
+//
+// What a group is (its sources, its cell's direction, whether it ends a partial
+// sum) is worked out by one thread a group, a window of groups at a time, and
+// read back as two words: worked out by each producer for itself it took 87 scalar
+// operations a group, more than the 75 vector operations of its pairs (65k
+// particles 226 -> 184 us, VJP 268 -> 238).
 template <int P>
 struct WideSmem {
+    static constexpr int kThreads = 64 * (P + 3);
+    static constexpr int kWindow = kThreads / P * P;   // whole rounds
     float4 terms[2][P][4][64];   // per buffer and group: f, then the components of e,
                                  // four pairs a lane
-    int ends[2][P];
+    int beg[128], cnt[128], end[128];   // source cells in order: first slot, sources,
+                                        // groups up to and with the cell
+    int2 group[kThreads];               // first slot, and what Group unpacks
     int item;
 };
 
-// The source cells of an item in order (c = 25 (dx+2) + 5 (dy+2) + dz+2), cut
+// The source cells of an item in order (c = 25 (dx+2) + 5 (dy+2) + dz+2) are cut
 // into groups of at most four sources of one cell, and of one partial sum in
-// the compensated mode: lane l holds cells l and l + 64.
-struct CellGroups {
-    int beg[2], cnt[2];     // first slot, sources
-    int first[2], end[2];   // groups before the cell, and with it
-};
-
+// the compensated mode (gpb groups in a full one).
 template <bool COMP>
 __device__ __forceinline__ int groups_of(int n, int flush, int gpb) {
     if constexpr (!COMP) return (n + 3) >> 2;
@@ -761,57 +790,62 @@ __device__ __forceinline__ int groups_of(int n, int flush, int gpb) {
     return full * gpb + ((n - full * flush + 3) >> 2);
 }
 
-// One group: its sources [j, j + count), its cell's direction, and whether it
-// ends a partial sum.
-struct Group {
-    int j, count, c;
-    bool ends;
-};
-template <bool COMP>
-__device__ __forceinline__ Group group_of(const CellGroups &G, int k, int flush, int gpb,
-                                          uint32_t gpb_inv) {
-    Group g;
-    const int c = (int)__popcll(__ballot(G.end[0] <= k)) + (int)__popcll(__ballot(G.end[1] <= k));
-    const int l = c & 63;
-    int beg, cnt, first;
-    if (c < 64) {
-        beg = __builtin_amdgcn_readlane(G.beg[0], l);
-        cnt = __builtin_amdgcn_readlane(G.cnt[0], l);
-        first = __builtin_amdgcn_readlane(G.first[0], l);
-    } else {
-        beg = __builtin_amdgcn_readlane(G.beg[1], l);
-        cnt = __builtin_amdgcn_readlane(G.cnt[1], l);
-        first = __builtin_amdgcn_readlane(G.first[1], l);
-    }
-    const int i = k - first;
-    int from = 0, at = 4 * i, upto = cnt;
+// Group k, by one thread.
+template <bool COMP, int P>
+__device__ __forceinline__ int2 pack_group(const WideSmem<P> &sm, int k, int flush, int gpb) {
+    int c = 0;   // the cell: the first with end > k
+#pragma unroll
+    for (int step = 64; step >= 1; step >>= 1)
+        if (sm.end[c + step - 1] <= k) c += step;
+    const int cnt = sm.cnt[c];
+    const int i = k - (sm.end[c] - groups_of<COMP>(cnt, flush, gpb));
+    int at = 4 * i, upto = cnt;
     if constexpr (COMP) {
-        // i / gpb: i < 2^25 (a cell's groups), exact for gpb_inv = ceil(2^32 / gpb)
-        // up to i gpb < 2^32
-        const int b = gpb == 1 ? i : (int)__umulhi((uint32_t)i, gpb_inv);
-        from = b * flush;
+        const int b = i / gpb, from = b * flush;
         at = from + 4 * (i - b * gpb);
         upto = min(cnt, from + flush);
     }
-    g.j = beg + at;
-    g.count = min(4, upto - at);
-    g.c = c;
-    g.ends = at + 4 >= upto;
-    return g;
+    const int r = c / 5, dx = r / 5 - 2, dy = r % 5 - 2, dz = c % 5 - 2;
+    const bool inner = dx >= -1 && dx <= 1 && dy >= -1 && dy <= 1 && dz >= -1 && dz <= 1;
+    return make_int2(sm.beg[c] + at, (min(4, upto - at) - 1) | (at + 4 >= upto ? 4 : 0) |
+                                         (inner ? 8 : 0) | (dx + 2) << 4 | (dy + 2) << 8 |
+                                         (dz + 2) << 12);
 }
+struct Group {
+    int count;
+    bool ends, inner;
+    int dx, dy, dz;
+    __device__ __forceinline__ explicit Group(int w)
+        : count((w & 3) + 1), ends(w & 4), inner(w & 8), dx(((w >> 4) & 15) - 2),
+          dy(((w >> 8) & 15) - 2), dz((w >> 12) - 2) {}
+};
 
-// Four records from slot j on; past the array's end (the last cell's last
-// group) each is read by itself, the last valid slot again.
+// Four records from slot j on; past the array's end the last valid slot again.
+// Accelerations by vector loads of one address (zero: a lane register that
+// holds 0): operations on scalar registers issue at half the rate.  The VJP's 32
+// registers would cost it a workgroup a CU: scalar loads.
 template <int MODE>
-__device__ __forceinline__ Rec<4 * (MODE == 0 ? 4 : 8)> load_group(cfloat *src, int j, int n) {
+__device__ __forceinline__ Rec<4 * (MODE == 0 ? 4 : 8)> load_group(cfloat *src, int j, int n,
+                                                                   int zero) {
     constexpr int W = MODE == 0 ? 4 : 8;
-    if (j + 4 <= n) return load_rec<4 * W>(src + (int64_t)W * j);
     Rec<4 * W> r;
+    if constexpr (MODE == 0) {
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-        const Rec<W> x = load_rec<W>(src + (int64_t)W * min(j + u, n - 1));
+        for (int u = 0; u < 4; ++u) {
+            gfloat *p = (gfloat *)src + (int64_t)W * min(j + u, n - 1) + zero;
+            // (only what is used: a dead register of a load in flight would be
+            // taken for something else, which waits for the load)
 #pragma unroll
-        for (int i = 0; i < W; ++i) r.w[W * u + i] = x.w[i];
+            for (int i = 0; i < 3; ++i) r.w[W * u + i] = p[i];
+        }
+    } else {
+        if (j + 4 <= n) return load_rec<4 * W>(src + (int64_t)W * j);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const Rec<W> x = load_rec<W>(src + (int64_t)W * min(j + u, n - 1));
+#pragma unroll
+            for (int i = 0; i < W; ++i) r.w[W * u + i] = x.w[i];
+        }
     }
     return r;
 }
@@ -903,9 +937,7 @@ __device__ __forceinline__ void wide_items(WideSmem<P> &sm, const DevBox *__rest
         const bool active = lane < g;   // lanes past the g sinks repeat sink 0
         const int slot = s0 + (active ? lane : 0);
         const int flush = uni(B.flush), gpb = (flush + 3) >> 2;
-        const uint32_t gpb_inv = 0xffffffffu / (uint32_t)gpb + 1u;   // unused for gpb = 1
-        CellGroups G;
-        {
+        if (wave == 0) {
             int ng[2];
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
@@ -913,112 +945,123 @@ __device__ __forceinline__ void wide_items(WideSmem<P> &sm, const DevBox *__rest
                 const int cell = (wrapk(cx + r / 5 - 2, K) * K + wrapk(cy + r % 5 - 2, K)) * K +
                                  wrapk(z + c % 5 - 2, K);
                 const int b = max(cs[cell], 0), e = min(cs[cell + 1], B.n);
-                G.beg[h] = b;
-                G.cnt[h] = lane + 64 * h < 125 ? max(e - b, 0) : 0;
-                ng[h] = groups_of<COMP>(G.cnt[h], flush, gpb);
+                const int cnt = lane + 64 * h < 125 ? max(e - b, 0) : 0;
+                sm.beg[lane + 64 * h] = b;
+                sm.cnt[lane + 64 * h] = cnt;
+                ng[h] = groups_of<COMP>(cnt, flush, gpb);
             }
-            G.end[0] = scan_lanes<64>(ng[0]);
-            G.end[1] = scan_lanes<64>(ng[1]) + __builtin_amdgcn_readlane(G.end[0], 63);
-#pragma unroll
-            for (int h = 0; h < 2; ++h) G.first[h] = G.end[h] - ng[h];
+            const int e0 = scan_lanes<64>(ng[0]), e1 = scan_lanes<64>(ng[1]);
+            sm.end[lane] = e0;
+            sm.end[lane + 64] = e1 + __builtin_amdgcn_readlane(e0, 63);
         }
-        const int ngroups = __builtin_amdgcn_readlane(G.end[1], 63);
-        const int rounds = (ngroups + P - 1) / P;
-        if (wave < P) {
-            const float4 oi = ld_global4((gfloat *)B.off, slot);
-            float4 vi = make_float4(0.f, 0.f, 0.f, 0.f);
-            if constexpr (MODE == 1)
-                vi = ld_global4((gfloat *)cot_sorted, 2 * (B.base + slot) + 1);
-            Coef k{B.cA, B.cB, B.cC, 2.0f * B.cC, B.eps * B.eps, B.r2floor};
-            in_vector(k.floor);
-            const bool fast = B.outer_newton != 0, plummer = B.plummer != 0;
-            cfloat *src =
-                MODE == 0 ? (cfloat *)B.off : (cfloat *)(cot_sorted + 2 * B.base);
-            int kg = wave;
-            Group gr = group_of<COMP>(G, min(kg, ngroups - 1), flush, gpb, gpb_inv);
-            auto rec = load_group<MODE>(src, gr.j, B.n);
-            for (int t = 0; t <= rounds; ++t) {
-                if (kg < ngroups) {
-                    const int c = gr.c, r = c / 5;
-                    const int dx = r / 5 - 2, dy = r % 5 - 2, dz = c % 5 - 2;
-                    const float xs = oi.x - (float)dx, ys = oi.y - (float)dy,
-                                zs = oi.z - (float)dz;
-                    const bool inner = dx >= -1 && dx <= 1 && dy >= -1 && dy <= 1 && dz >= -1 &&
-                                       dz <= 1;
+        const bool producer = wave < P;
+        const int comp = wave - P;   // of a consumer
+        const float4 oi = ld_global4((gfloat *)B.off, slot);
+        const int dst = gp(B.order)[slot];
+        float4 vi = make_float4(0.f, 0.f, 0.f, 0.f);
+        if constexpr (MODE == 1) vi = ld_global4((gfloat *)cot_sorted, 2 * (B.base + slot) + 1);
+        Coef k{B.cA, B.cB, B.cC, 2.0f * B.cC, B.eps * B.eps, B.r2floor};
+        in_vector(k.floor);
+        const bool fast = B.outer_newton != 0, plummer = B.plummer != 0;
+        cfloat *src = MODE == 0 ? (cfloat *)B.off : (cfloat *)(cot_sorted + 2 * B.base);
+        int zero;
+        asm volatile("v_mov_b32 %0, 0" : "=v"(zero));
+        float p = 0.f, sum = 0.f, low = 0.f;
+        __syncthreads();
+        const int ngroups = uni(sm.end[127]);
+        for (int w0 = 0; w0 < ngroups; w0 += sm.kWindow) {
+            sm.group[threadIdx.x] = pack_group<COMP, P>(
+                sm, min(w0 + (int)threadIdx.x, ngroups - 1), flush, gpb);
+            __syncthreads();
+            const int last = min(sm.kWindow, ngroups - w0) - 1;   // the window's last group
+            const int rounds = last / P + 1;
+            if (producer) {
+                // (past the last group a producer repeats it, and nobody reads that)
+                int kg = wave;
+                int2 w = sm.group[min(kg, last)], next = sm.group[min(kg + P, last)];
+                auto rec = load_group<MODE>(src, uni(w.x), B.n, zero);
+                for (int t = 0; t < rounds; ++t) {
+                    const Group gr(uni(w.y));
+                    const float xs = oi.x - (float)gr.dx, ys = oi.y - (float)gr.dy,
+                                zs = oi.z - (float)gr.dz;
                     const Sep<MODE, 4> d = separations<MODE, 4>(rec, xs, ys, zs, vi);
-                    const int count = gr.count;
-                    const bool e = gr.ends;
-                    kg += P;
-                    gr = group_of<COMP>(G, min(kg, ngroups - 1), flush, gpb, gpb_inv);
+                    w = next;
                     __builtin_amdgcn_sched_barrier(0);
-                    rec = load_group<MODE>(src, gr.j, B.n);
+                    rec = load_group<MODE>(src, uni(w.x), B.n, zero);
+                    kg += P;
+                    next = sm.group[min(kg + P, last)];
                     __builtin_amdgcn_sched_barrier(0);
                     float f[4], ex[4], ey[4], ez[4];
-                    if (!plummer && (!fast || inner))
+                    if (!plummer && (!fast || gr.inner))
                         pair_terms<MODE, true>(d, k, f, ex, ey, ez);
                     else
                         pair_terms<MODE, false>(d, k, f, ex, ey, ez);
                     // past the group's sources: 0 times 0 (a finite e would do
                     // for the sum, but another cell's cotangent may not be)
+                    if (gr.count < 4) {
 #pragma unroll
-                    for (int u = 1; u < 4; ++u)
-                        if (u >= count) f[u] = ex[u] = ey[u] = ez[u] = 0.f;
+                        for (int u = 1; u < 4; ++u)
+                            if (u >= gr.count) f[u] = ex[u] = ey[u] = ez[u] = 0.f;
+                    }
                     float4(*o)[64] = sm.terms[t & 1][wave];
                     o[0][lane] = make_float4(f[0], f[1], f[2], f[3]);
                     o[1][lane] = make_float4(ex[0], ex[1], ex[2], ex[3]);
                     o[2][lane] = make_float4(ey[0], ey[1], ey[2], ey[3]);
                     o[3][lane] = make_float4(ez[0], ez[1], ez[2], ez[3]);
-                    if (lane == 0) sm.ends[t & 1][wave] = e ? 1 : 0;
+                    __syncthreads();
                 }
                 __syncthreads();
-            }
-        } else {
-            const int comp = wave - P;
-            const int dst = gp(B.order)[slot];
-            float p = 0.f, sum = 0.f, low = 0.f;
-            for (int t = 0; t <= rounds; ++t) {
-                if (t > 0) {
-                    const int buf = (t - 1) & 1, m = min(P, ngroups - (t - 1) * P);
-                    const int last = COMP ? sm.ends[buf][lane < P ? lane : 0] : 0;
-                    float4 f[P], e[P];
+            } else {
+                for (int t = 0; t <= rounds; ++t) {
+                    if (t > 0) {
+                        const int buf = (t - 1) & 1, at = (t - 1) * P;
+                        const int ends = COMP ? sm.group[at + min(lane, P - 1)].y : 0;
+                        constexpr int kAhead = 5;   // groups read ahead
+                        float4 f[P], e[P];
+                        auto read = [&](int i) {
+                            f[i] = sm.terms[buf][i][0][lane];
+                            e[i] = sm.terms[buf][i][1 + comp][lane];
+                        };
 #pragma unroll
-                    for (int i = 0; i < P; ++i) {
-                        f[i] = sm.terms[buf][i][0][lane];
-                        e[i] = sm.terms[buf][i][1 + comp][lane];
-                    }
+                        for (int i = 0; i < min(P, kAhead); ++i) read(i);
 #pragma unroll
-                    for (int i = 0; i < P; ++i) {
-                        if (i < m) {
-                            p = __builtin_fmaf(f[i].x, e[i].x, p);
-                            p = __builtin_fmaf(f[i].y, e[i].y, p);
-                            p = __builtin_fmaf(f[i].z, e[i].z, p);
-                            p = __builtin_fmaf(f[i].w, e[i].w, p);
-                            if constexpr (COMP) {
-                                if (__builtin_amdgcn_readlane(last, i)) {
-                                    kahan(sum, low, p);
-                                    p = 0.f;
+                        for (int i = 0; i < P; ++i) {
+                            if (i + kAhead < P) read(i + kAhead);
+                            if (at + i <= last) {
+                                p = __builtin_fmaf(f[i].x, e[i].x, p);
+                                p = __builtin_fmaf(f[i].y, e[i].y, p);
+                                p = __builtin_fmaf(f[i].z, e[i].z, p);
+                                p = __builtin_fmaf(f[i].w, e[i].w, p);
+                                if constexpr (COMP) {
+                                    if (__builtin_amdgcn_readlane(ends, i) & 4) {
+                                        kahan(sum, low, p);
+                                        p = 0.f;
+                                    }
                                 }
                             }
                         }
                     }
+                    __syncthreads();
                 }
-                __syncthreads();
             }
-            if (active && dst >= 0 && dst < B.n)
-                gp(B.out)[3 * (int64_t)dst + comp] = (COMP ? sum - low : p) * B.scale;
         }
+        if (!producer && active && dst >= 0 && dst < B.n)
+            gp(B.out)[3 * (int64_t)dst + comp] = (COMP ? sum - low : p) * B.scale;
     }
 }
 
 constexpr int kProducers = 5;
 constexpr int kWideThreads = 64 * (kProducers + 3);
 template <int MODE, bool COMP>
-__global__ void __launch_bounds__(kWideThreads)
+__global__ void __launch_bounds__(kWideThreads) __attribute__((amdgpu_waves_per_eu(6)))
 k_dense_wide(const DevBox *__restrict__ boxes, const Item *__restrict__ items,
              const uint32_t *__restrict__ totals, uint32_t *counter,
              const float4 *__restrict__ cot_sorted) {
     __shared__ WideSmem<kProducers> sm;
-    wide_items<MODE, COMP, kProducers>(sm, boxes, items, (int)totals[0], counter, cot_sorted);
+    const int nitems = (int)totals[0], heavy = (int)totals[3];
+    wide_items<MODE, COMP, kProducers>(sm, boxes, items, heavy, counter, cot_sorted);
+    dense_items<MODE, COMP>((int)(threadIdx.x & 63), boxes, items + heavy, nitems - heavy,
+                            counter + 1, cot_sorted);
 }
 
 // ------------------------------------------------------------------ light path
@@ -1657,11 +1700,12 @@ hipError_t launch_narrow(const DevBox *d_boxes, const TilePlan &tp, const float4
 }
 
 // k_dense_wide takes the dense items of calls of at most this many particles
-// (over all boxes).  Whole force calls with k_dense / k_dense_wide, clustered
-// boxes, us: 20k particles plain 139 / 96, VJP 204 / 116; 50k 161 / 120, 267 /
-// 156; 131k 247 / 238 (compensated 263 / 270), 429 / 303; 262k 326 / 393, 632 /
-// 506; 524k 492 / 732, 885 / 959.
-constexpr int64_t kWideMaxAccel = 100000, kWideMaxVjp = 300000;
+// (over all boxes): above, the card is full with one wave an item and nothing
+// waits for the heaviest one.  Whole force calls with k_dense / k_dense_wide,
+// clustered boxes, us: 65k particles plain 285 / 180, VJP 500 / 233; 131k 245 / 206,
+// 433 / 284; 262k 304 / 264, 596 / 412; 400k 393 / 402, 719 / 601; 524k 483 / 486,
+// 887 / 727; 700k 562 / 569, 845 / 876; 1M 775 / 759, 1144 / 1169.
+constexpr int64_t kWideMaxAccel = 350000, kWideMaxVjp = 600000;
 
 template <int MODE, bool COMP>
 hipError_t launch_dense_wide(const DevBox *d_boxes, const TilePlan &tp, const float4 *cot,
@@ -1729,11 +1773,11 @@ hipError_t launch_force(const DevBox *d_boxes, const TilePlan &tp, const float4 
     if ((e = hipEventRecord(ss.fork, s)) != hipSuccess) return e;
     for (int k = 0; k < 2; ++k)
         if ((e = hipStreamWaitEvent(ss.s[k], ss.fork, 0)) != hipSuccess) return e;
+    if ((e = launch_dense<MODE, COMP>(d_boxes, tp, cot, f4 != nullptr, s)) != hipSuccess) return e;
     if ((e = launch_light<MODE, COMP>(d_boxes, tp, cot, ss.s[0])) != hipSuccess) return e;
     if ((e = hipEventRecord(ss.join[0], ss.s[0])) != hipSuccess) return e;
     if ((e = launch_narrow<MODE, COMP>(d_boxes, tp, cot, ss.s[1])) != hipSuccess) return e;
     if ((e = hipEventRecord(ss.join[1], ss.s[1])) != hipSuccess) return e;
-    if ((e = launch_dense<MODE, COMP>(d_boxes, tp, cot, f4 != nullptr, s)) != hipSuccess) return e;
     if (f4 && (e = f4_ring_launch(d_boxes, *f4, COMP, s)) != hipSuccess) return e;
     for (int k = 0; k < 2; ++k)
         if ((e = hipStreamWaitEvent(s, ss.join[k], 0)) != hipSuccess) return e;
@@ -1791,7 +1835,8 @@ hipError_t plan_launch(const DevBox *d_boxes, int nbox, const TilePlan &tp, floa
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_plan_emit, dim3(cb, (unsigned)nbox), dim3(256), 0, s, d_boxes,
                        (const uint32_t *)tp.cellinfo, (const uint32_t *)tp.bucket_cnt,
-                       tp.bucket_cnt + kKinds * kBuckets, tp.totals, tp.dense, tp.light);
+                       tp.bucket_cnt + kKinds * kBuckets, tp.totals, tp.dense, tp.light,
+                       cot ? kHeavyShareVjp : kHeavyShareAccel);
     return hipGetLastError();
 }
 
