@@ -1597,13 +1597,14 @@ k_small(const DevBox *__restrict__ boxes, const Item *__restrict__ dense,
 
 // ------------------------------------------------------------------ launches
 
+// As many workgroups as the card holds, of at most `most` a CU.
 template <typename Kern>
-int persistent_grid(Kern kern, int threads) {
+int persistent_grid(Kern kern, int threads, int most = 1 << 20) {
     int dev = 0, ncu = 0, per = 0;
     (void)hipGetDevice(&dev);
     (void)hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);
     (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, kern, threads, 0);
-    return std::max(1, ncu) * std::max(1, per);
+    return std::max(1, ncu) * std::max(1, std::min(per, most));
 }
 
 // A persistent grid of `most` workgroups, or fewer where the call cannot have
@@ -1706,6 +1707,7 @@ hipError_t launch_narrow(const DevBox *d_boxes, const TilePlan &tp, const float4
 // 433 / 284; 262k 304 / 264, 596 / 412; 400k 393 / 402, 719 / 601; 524k 483 / 486,
 // 887 / 727; 700k 562 / 569, 845 / 876; 1M 775 / 759, 1144 / 1169.
 constexpr int64_t kWideMaxAccel = 350000, kWideMaxVjp = 600000;
+constexpr int64_t kDenseCapAccel = 5000000, kDenseCapVjp = 2500000;   // see launch_dense
 
 template <int MODE, bool COMP>
 hipError_t launch_dense_wide(const DevBox *d_boxes, const TilePlan &tp, const float4 *cot,
@@ -1720,13 +1722,23 @@ hipError_t launch_dense_wide(const DevBox *d_boxes, const TilePlan &tp, const fl
 
 template <int MODE, bool COMP>
 hipError_t launch_dense(const DevBox *d_boxes, const TilePlan &tp, const float4 *cot, bool f4,
-                        hipStream_t s) {
+                        bool concurrent, hipStream_t s) {
     if (!f4 && tp.particles <= (MODE == 0 ? kWideMaxAccel : kWideMaxVjp))
         return launch_dense_wide<MODE, COMP>(d_boxes, tp, cot, s);
-    // every XCD queue needs at least one workgroup: a multiple of kXcds
-    static const int most =
+    // Beside the light kernels twelve waves a CU (VJP sixteen) are enough, and
+    // leave them the slots; where dense items last after the light ones, which
+    // they do in the largest boxes, they need all.  Full / capped, clustered, us:
+    // accelerations 1M 762 / 739, 2.1M 1391 / 1365, 4M 2532 / 2506 (more clustered
+    // 3266 / 3232, 8M 6755 / 7082); VJP 1M 1134 / 1077, 2.1M 2186 / 2161, 4M 4173 /
+    // 4203.  Every XCD queue needs at least one workgroup: a multiple of kXcds.
+    const bool cap =
+        concurrent && !f4 && tp.particles <= (MODE == 0 ? kDenseCapAccel : kDenseCapVjp);
+    static const int full =
         (persistent_grid(k_dense<MODE, COMP>, kUnit) + kXcds - 1) / kXcds * kXcds;
-    const int grid = grid_for(most, tp.max_dense, kXcds);
+    static const int capped =
+        (persistent_grid(k_dense<MODE, COMP>, kUnit, MODE == 0 ? 12 : 16) + kXcds - 1) / kXcds *
+        kXcds;
+    const int grid = grid_for(cap ? capped : full, tp.max_dense, kXcds);
     hipLaunchKernelGGL((k_dense<MODE, COMP>), dim3(grid), dim3(kUnit), 0, s, d_boxes,
                        (const Item *)tp.dense, (const uint32_t *)tp.totals, tp.counter, cot);
     return hipGetLastError();
@@ -1760,7 +1772,7 @@ hipError_t launch_force(const DevBox *d_boxes, const TilePlan &tp, const float4 
     if (!concurrent) {   // the kernels in turn on the caller's stream
         if ((e = launch_light<MODE, COMP>(d_boxes, tp, cot, s)) != hipSuccess) return e;
         if ((e = launch_narrow<MODE, COMP>(d_boxes, tp, cot, s)) != hipSuccess) return e;
-        if ((e = launch_dense<MODE, COMP>(d_boxes, tp, cot, f4 != nullptr, s)) != hipSuccess) return e;
+        if ((e = launch_dense<MODE, COMP>(d_boxes, tp, cot, f4 != nullptr, concurrent, s)) != hipSuccess) return e;
         if (f4 && (e = f4_ring_launch(d_boxes, *f4, COMP, s)) != hipSuccess) return e;
         return hipSuccess;
     }
@@ -1773,7 +1785,7 @@ hipError_t launch_force(const DevBox *d_boxes, const TilePlan &tp, const float4 
     if ((e = hipEventRecord(ss.fork, s)) != hipSuccess) return e;
     for (int k = 0; k < 2; ++k)
         if ((e = hipStreamWaitEvent(ss.s[k], ss.fork, 0)) != hipSuccess) return e;
-    if ((e = launch_dense<MODE, COMP>(d_boxes, tp, cot, f4 != nullptr, s)) != hipSuccess) return e;
+    if ((e = launch_dense<MODE, COMP>(d_boxes, tp, cot, f4 != nullptr, concurrent, s)) != hipSuccess) return e;
     if ((e = launch_light<MODE, COMP>(d_boxes, tp, cot, ss.s[0])) != hipSuccess) return e;
     if ((e = hipEventRecord(ss.join[0], ss.s[0])) != hipSuccess) return e;
     if ((e = launch_narrow<MODE, COMP>(d_boxes, tp, cot, ss.s[1])) != hipSuccess) return e;
