@@ -650,8 +650,8 @@ static int step_common(int nbox, const nf_box *boxes, const std::vector<StepIO> 
     char *w = static_cast<char *>(ws);
     d_tab = reinterpret_cast<DevBox *>(w + L.table_off);
     d_io = reinterpret_cast<StepIO *>(w + L.stepio_off);
-    hipError_t e = upload(tab.data(), sizeof(DevBox) * tab.size(), d_tab, s);
-    if (e == hipSuccess) e = upload(io.data(), sizeof(StepIO) * io.size(), d_io, s);
+    hipError_t e = upload_pair(tab.data(), sizeof(DevBox) * tab.size(), L.table_off, io.data(),
+                               sizeof(StepIO) * io.size(), L.stepio_off, w, s);
     if (e != hipSuccess) return fail(NF_EHIP, std::string("upload: ") + hipGetErrorString(e));
     return NF_OK;
 }
@@ -742,8 +742,21 @@ int nf_kick_drift(int nbox, const nf_box *boxes, const float *const *acc, float 
         hipStream_t s = static_cast<hipStream_t>(stream);
         DevBox *d_tab = nullptr;
         StepIO *d_io = nullptr;
-        if ((rc = step_common(nbox, boxes, io, ws, ws_bytes, s, L, d_tab, d_io))) return rc;
-        hipError_t e = kick_drift_launch(d_tab, d_io, nbox, L.max_n, kick, drift, s);
+        Chunk c;
+        const size_t tab_bytes = sizeof(DevBox) * (size_t)nbox;
+        if (tab_bytes + sizeof(StepIO) * (size_t)nbox <= (size_t)kChunkBytes) {
+            // both tables as an argument of the one kernel
+            if ((rc = check_ws(L, ws, ws_bytes))) return rc;
+            std::string why;
+            if ((rc = check_device(why))) return fail(rc, why);
+            std::vector<DevBox> tab((size_t)nbox);
+            for (int b = 0; b < nbox; ++b) fill_geometry(boxes[b], L, b, tab[b]);
+            std::memcpy(c.bytes, tab.data(), tab_bytes);
+            std::memcpy(c.bytes + tab_bytes, io.data(), sizeof(StepIO) * (size_t)nbox);
+        } else if ((rc = step_common(nbox, boxes, io, ws, ws_bytes, s, L, d_tab, d_io))) {
+            return rc;
+        }
+        hipError_t e = kick_drift_launch(c, d_tab, d_io, nbox, L.max_n, kick, drift, s);
         if (e != hipSuccess) return fail(NF_EHIP, std::string("kick/drift: ") + hipGetErrorString(e));
         g_last_error.clear();
         return NF_OK;

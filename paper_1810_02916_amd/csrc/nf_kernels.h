@@ -144,8 +144,9 @@ hipError_t step_stats_launch(const DevBox *d_boxes, const StepIO *d_io, int nbox
 hipError_t step_choose_launch(const DevBox *d_boxes, const StepIO *d_io, int nbox,
                               double *partial, const double *glob, const StepChoice &ch,
                               double *bounds, hipStream_t s);
-hipError_t kick_drift_launch(const DevBox *d_boxes, const StepIO *d_io, int nbox, int64_t max_n,
-                             double kick, double drift, hipStream_t s);
+// d_boxes null: the boxes' descriptors, then their StepIO, are in c.
+hipError_t kick_drift_launch(const Chunk &c, const DevBox *d_boxes, const StepIO *d_io, int nbox,
+                             int64_t max_n, double kick, double drift, hipStream_t s);
 
 // Force launches.  `items` and `nitems` describe the work list built on the
 // host side of the call (see nf_accel.hip).

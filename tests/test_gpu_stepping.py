@@ -114,3 +114,24 @@ def test_kick_drift_bit_exact_and_batched():
     # the drifted positions bin again (positions are wrapped by the binning)
     b2 = nfp.rebin(b)
     assert all(n == 0 for n in b2.nbad())
+
+
+@pytest.mark.parametrize("nbox", [1, 13, 14, 15, 40])
+def test_kick_drift_descriptors_by_argument_and_from_memory(nbox):
+    """The boxes' tables travel as an argument of the kernel up to 3840 bytes
+    (13 or 14 boxes) and through the workspace above; an empty box among them."""
+    rng = np.random.default_rng(nbox)
+    ns = [0 if b == 3 else 1 + 37 * b for b in range(nbox)]
+    x0 = [rng.uniform(size=(n, 3)) for n in ns]
+    v0 = [rng.normal(size=(n, 3)).astype(np.float32) for n in ns]
+    a0 = [rng.normal(size=(n, 3)).astype(np.float32) for n in ns]
+    pos = [_t(x, torch.float64) for x in x0]
+    vel = [_t(v, torch.float32) for v in v0]
+    acc = [_t(a, torch.float32) for a in a0]
+    b = nfp.bin_particles_batched(pos, [5] * nbox, [1.0] * nbox, [0.01] * nbox)
+    nfp.kick_drift(b, acc, vel, pos, 0.3, -0.02)
+    for x, v, a, p, u in zip(x0, v0, a0, pos, vel):
+        if len(x):
+            xr, vr = oracle.kick_drift(x, v, a, 0.3, -0.02)
+            assert u.cpu().numpy().tobytes() == vr.tobytes()
+            assert p.cpu().numpy().tobytes() == xr.tobytes()
