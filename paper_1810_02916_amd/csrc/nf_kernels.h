@@ -88,7 +88,8 @@ hipError_t plan_export_launch(const TilePlan &tp, int32_t *items, int64_t max_it
                               int64_t *counts, hipStream_t s);
 // mode 0: accelerations, 1: VJP (cot = cotangents in sorted order).
 // concurrent: the light and narrow kernels run on the library's side streams
-// alongside the dense kernel; otherwise all three run in turn on s.
+// alongside the dense kernel, or, in a small call, all three item classes in one
+// kernel on s; otherwise all three run in turn on s.
 hipError_t tile_launch(const DevBox *d_boxes, int mode, bool compensated, const TilePlan &tp,
                        const float4 *cot, bool concurrent, hipStream_t s,
                        const F4Plan *f4 = nullptr);

@@ -1,5 +1,5 @@
 // nf_tile.hip -- tiled near-field kernels for gfx950: a device-side planner
-// that cuts the cell grid into work items, and two persistent kernels that
+// that cuts the cell grid into work items, and persistent kernels that
 // sum the pair forces of Eq. 2 (Sec. 4.3) over the 5x5x5 cell block of
 // Sec. 2.1.
 //
@@ -11,7 +11,8 @@
 //               scalar loads and enter the arithmetic as SGPR operands, and
 //               the sink is shifted into each source cell's frame.  No LDS, so
 //               many waves fit on a CU and hide the load latency.  Items run
-//               heaviest neighbourhood first.
+//               heaviest neighbourhood first; the heaviest ones of a call of
+//               few items by a whole workgroup each.
 //   * light  -- a smaller last chunk (all sinks of a cell of fewer than
 //               dense_min particles), one item per 4-wave workgroup.  The 125
 //               source cells are staged in LDS in the sink cell's own frame,
@@ -25,6 +26,7 @@
 //               per-item costs that do not shrink with g (item setup, the
 //               per-wave header, the slice tree) are paid by one wave instead
 //               of four.
+// Small calls run all three classes in one launch (k_small).
 // The class boundaries (dense_min, narrow_max), the staging windows of the
 // light and narrow kernels and the compensated partial-sum length are tile
 // choices of the caller (nf_box), picked by the autotuner.
@@ -1750,9 +1752,10 @@ hipError_t launch_dense(const DevBox *d_boxes, const TilePlan &tp, const float4 
 // which it is built for).  Below, a call is bound by the host: a fork to two
 // streams and the joins take 50 us of it.  Above, a workgroup per CU is too few
 // for the dense items.  Whole calls, three kernels on three streams / k_small,
-// us, clustered: 1000 particles plain 82 / 28, VJP 65 / 37; 4096 92 / 48, 103 /
-// 60; 16384 107 / 60, 129 / 75; 50k 139 / 124, 179 / 177; 65k 210 / 224, 259 /
-// 267; uniform 32768 74 / 55, 94 / 80.
+// us, clustered: 1000 particles plain 82 / 28, VJP 65 / 37; 4096 92 / 47, 103 /
+// 52; 50k 133 / 122, 176 / 167 (compensated 134 / 140, 183 / 183); 65k 179 / 173,
+// 234 / 232 (compensated 174 / 202, 246 / 271); 100k 184 / 217, 269 / 297; uniform
+// 32768 89 / 56, 107 / 80.
 constexpr int64_t kSmallMax = 60000;
 
 template <int MODE, bool COMP>
