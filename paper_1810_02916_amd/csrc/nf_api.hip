@@ -781,16 +781,12 @@ int nf_multipoles(int nbox, const nf_box *boxes, int order, float *const *mom, v
         if ((rc = check_device(why))) return fail(rc, why);
         std::vector<DevBox> tab((size_t)nbox);
         std::vector<int64_t> rbase((size_t)nbox + 1, 0);
-        int64_t max_ranges = 1;
         for (int b = 0; b < nbox; ++b) {
             fill_geometry(boxes[b], L, b, tab[b]);
             tab[b].out = mom[b];
-            const int64_t r = multipole_ranges(boxes[b].n, (int64_t)tab[b].ncell);
-            rbase[b + 1] = rbase[b] + r;
-            max_ranges = std::max(max_ranges, r);
+            rbase[b + 1] = rbase[b] + multipole_ranges(boxes[b].n, (int64_t)tab[b].ncell);
         }
-        if (max_ranges > INT32_MAX || L.mp_max_pieces > INT32_MAX ||
-            (size_t)(rbase[nbox] + nbox) * 4 > L.mp_first_bytes)
+        if ((size_t)(rbase[nbox] + nbox) * 4 > L.mp_first_bytes)
             return fail(NF_EUNSUPPORTED, "multipole partition exceeds the workspace plan");
         hipStream_t s = static_cast<hipStream_t>(stream);
         char *w = static_cast<char *>(ws);
@@ -798,7 +794,7 @@ int nf_multipoles(int nbox, const nf_box *boxes, int order, float *const *mom, v
         int64_t *d_rbase = reinterpret_cast<int64_t *>(w + L.mp_base_off);
         MpPlan mp;
         mp.max_ncell = L.max_ncell;
-        mp.max_ranges = max_ranges;
+        mp.ranges = rbase[nbox];
         mp.max_pieces = L.mp_max_pieces;
         mp.range_base = d_rbase;
         mp.first = reinterpret_cast<int32_t *>(w + L.mp_first_off);

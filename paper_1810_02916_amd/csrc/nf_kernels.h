@@ -109,7 +109,7 @@ struct MpPiece {
 };
 struct MpPlan {
     int64_t max_ncell = 0;          // largest per-box cell count
-    int64_t max_ranges = 0;         // largest per-box range count
+    int64_t ranges = 0;             // ranges over all boxes
     int64_t max_pieces = 0;         // bound on the pieces over all boxes
     const int64_t *range_base = nullptr;   // [nbox + 1] prefix of the range counts
     int32_t *first = nullptr;       // sum over boxes of (ranges + 1)

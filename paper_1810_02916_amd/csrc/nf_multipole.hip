@@ -235,25 +235,36 @@ __device__ __forceinline__ void piece_moments(const DevBox *__restrict__ boxes, 
     for (int j = 0; j < kUnitTerms; ++j) gp(partial)[U.idx[j]] = j < U.uk ? acc[j] : acc[0];
 }
 
-// Workgroup (x, y): piece y * npiece_blocks + x for x < npiece_blocks (the pieces
-// of all boxes; most grids have more such workgroups than pieces, and these end
-// at once), else run x - npiece_blocks of box y.
+// Workgroups in row-major order: the pieces of all boxes (most calls have more
+// such workgroups than pieces, and these end at once), then the runs of box 0, of
+// box 1, ...  One flat list: a row of the grid per box, as long as the longest,
+// held mostly idle workgroups for uneven boxes (63 boxes of 1000 particles beside
+// one of 2.1M: 577 us a call, 145 so).
 __global__ void __launch_bounds__(64)
-k_multipoles(const DevBox *__restrict__ boxes, const int64_t *__restrict__ range_base,
-             const int32_t *__restrict__ first, int p, int nterms, int npiece_blocks,
+k_multipoles(const DevBox *__restrict__ boxes, int nbox, const int64_t *__restrict__ range_base,
+             const int32_t *__restrict__ first, int p, int nterms,
              const MpPiece *__restrict__ pieces, const uint32_t *__restrict__ total,
              int64_t max_pieces, double *__restrict__ partial) {
     __shared__ __align__(16) double pw[kRows][kRowLen];   // powers of the staged particles
     static_assert(kChunk == 32, "one staged particle per lane");
-    const int box = blockIdx.y;
-    if ((int)blockIdx.x < npiece_blocks) {
-        const int64_t i = (int64_t)box * npiece_blocks + blockIdx.x;
-        if (i < min((int64_t)*total, max_pieces))
-            piece_moments(boxes, pieces[i], partial + i * kMaxTerms, p, pw);
+    const int64_t i = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
+    if (i < max_pieces) {
+        if (i < (int64_t)*total) piece_moments(boxes, pieces[i], partial + i * kMaxTerms, p, pw);
         return;
     }
-    const int w = (int)blockIdx.x - npiece_blocks;
-    if ((int64_t)w >= range_base[box + 1] - range_base[box]) return;   // whole workgroup
+    const int64_t run = i - max_pieces;
+    if (run >= range_base[nbox]) return;   // whole workgroup
+    // the last box whose runs start here or before, 64 candidates by one load
+    int box = 0;
+    for (int len = nbox; len > 1;) {
+        const int step = (len + 63) >> 6, at = (int)threadIdx.x * step;
+        const bool from = at < len && range_base[box + at] <= run;
+        const int k = (__popcll(__ballot(from)) - 1) * step;
+        box += k;
+        len = min(step, len - k);
+    }
+    box = __builtin_amdgcn_readfirstlane(box);
+    const int w = (int)(run - range_base[box]);
     const DevBox &B = boxes[box];
     const int32_t *f = first + range_base[box] + box;
     const int t = threadIdx.x;
@@ -265,7 +276,7 @@ k_multipoles(const DevBox *__restrict__ boxes, const int64_t *__restrict__ range
     const int c0 = f[w], c1 = f[w + 1];
     if (c0 >= c1) return;
     // each cell costs >= kCellCost, so a range holds at most kRange / kCellCost
-    // = 64 cells: lane k holds the start and end of the range's cell k, read
+    // = 16 cells: lane k holds the start and end of the range's cell k, read
     // back with readlane (uniform index, no memory wait)
     static_assert(kRange / kCellCost <= 64, "one cell of the range per lane");
     const int cbeg_l = t < c1 - c0 ? cs[c0 + t] : 0;
@@ -356,6 +367,31 @@ int multipole_big() { return kBig; }
 // Sum over big cells of ceil(n_c / kBig) <= n / kBig + (big cells) < 2 n / kBig.
 int64_t multipole_max_pieces(int64_t n) { return 2 * (n / kBig) + 1; }
 
+namespace {
+
+// The grid of k_multipoles.  A dimension of a launch holds fewer than 2^32 work
+// items, which the largest calls pass (K = 1024 needs 2^26 workgroups of 64):
+// rows of at most kMaxRow workgroups.
+constexpr int64_t kMaxRow = (int64_t)1 << 25;
+constexpr int64_t grid_rows(int64_t workgroups) {
+    return workgroups > kMaxRow ? (workgroups + kMaxRow - 1) / kMaxRow : 1;
+}
+constexpr int64_t grid_cols(int64_t workgroups) {
+    return workgroups > 0 ? (workgroups + grid_rows(workgroups) - 1) / grid_rows(workgroups) : 1;
+}
+constexpr bool grid_fits(int64_t n, int64_t ncell, int64_t nbox) {
+    const int64_t pieces = 2 * (n / kBig) + nbox;
+    const int64_t all = (n + kCellCost * ncell) / kRange + nbox + pieces;
+    return grid_cols(all) * 64 < (int64_t)1 << 32 && grid_rows(all) < 65536 &&
+           grid_cols(all) * grid_rows(all) >= all && 64 * pieces < (int64_t)1 << 32;
+}
+static_assert(grid_fits(0, 125, 1) && grid_fits(1 << 20, 1024 * 1024 * 1024, 1) &&
+                  grid_fits(INT32_MAX, 1290 * 1290 * 1290, 1) &&
+                  grid_fits(INT32_MAX, INT32_MAX, 4096),
+              "every call that is accepted can be launched");
+
+}  // namespace
+
 hipError_t multipole_launch(const DevBox *d_boxes, int nbox, const MpPlan &mp, int p,
                             hipStream_t s) {
     hipLaunchKernelGGL(k_mp_plan, dim3((unsigned)((mp.max_ncell + 1 + 255) / 256), (unsigned)nbox),
@@ -363,10 +399,10 @@ hipError_t multipole_launch(const DevBox *d_boxes, int nbox, const MpPlan &mp, i
                        mp.max_pieces);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    const unsigned piece_blocks = (unsigned)((mp.max_pieces + nbox - 1) / nbox);
-    hipLaunchKernelGGL(k_multipoles, dim3((unsigned)mp.max_ranges + piece_blocks, (unsigned)nbox),
-                       dim3(64), 0, s, d_boxes, mp.range_base, (const int32_t *)mp.first, p,
-                       multipole_terms(p), (int)piece_blocks, (const MpPiece *)mp.pieces,
+    const int64_t all = mp.max_pieces + mp.ranges;
+    hipLaunchKernelGGL(k_multipoles, dim3((unsigned)grid_cols(all), (unsigned)grid_rows(all)),
+                       dim3(64), 0, s, d_boxes, nbox, mp.range_base, (const int32_t *)mp.first, p,
+                       multipole_terms(p), (const MpPiece *)mp.pieces,
                        (const uint32_t *)mp.total, mp.max_pieces, mp.partial);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     hipLaunchKernelGGL(k_mp_combine, dim3((unsigned)std::max<int64_t>(1, mp.max_pieces)), dim3(64),

@@ -110,3 +110,39 @@ def test_multipoles_cells_around_chunk_run_and_piece_sizes(p):
     _check(pos[rng.permutation(len(pos))], K, L, p)
     empty = nfp.bin_particles(torch.empty((0, 3), dtype=torch.float64, device=DEV), K, L, 0.01)
     assert (nfp.multipoles(empty, p) == 0).all()
+
+
+def test_multipoles_of_uneven_boxes_equal_the_single_calls_bitwise():
+    """A batch of empty, tiny, sparse, large and one-cell boxes in any order:
+    every box's moments are those of the box alone."""
+    one_cell = (np.array([5, 0, 5]) + np.random.default_rng(3).uniform(0, 1, (700, 3))) / 6
+    specs = [(np.zeros((0, 3)), 7), (clustered_box(5000, 16, 12, 1.0, 1.5, 0.5, seed=5), 12),
+             (np.full((1, 3), 0.3), 5), (np.zeros((0, 3)), 5),
+             (clustered_box(200000, 58, 32, 1.0, 1.5, 0.5, seed=6), 32), (one_cell, 6),
+             (np.random.default_rng(4).uniform(0, 1, (900, 3)), 40), (np.zeros((0, 3)), 20)]
+    for order in (specs, specs[::-1]):
+        pos = [torch.from_numpy(np.ascontiguousarray(p)).to(DEV) for p, _ in order]
+        Ks = [K for _, K in order]
+        got = nfp.multipoles(nfp.bin_particles_batched(pos, Ks, [1.0] * len(Ks),
+                                                       [0.01] * len(Ks)), 4)
+        for x, K, g in zip(pos, Ks, got):
+            assert torch.equal(g, nfp.multipoles(nfp.bin_particles(x, K, 1.0, 0.01), 4))
+
+
+def test_multipoles_of_the_finest_grids():
+    """1024^3 cells: the launch passes what one grid dimension can hold (33 GB
+    of cell starts, moments and workspace)."""
+    K = 1024
+    rng = np.random.default_rng(82)
+    pos = np.concatenate([rng.uniform(0, 1, (3000, 3)),
+                          (np.array([1023, 1023, 1023]) + rng.uniform(0, 1, (300, 3))) / K,
+                          (np.array([0, 0, 0]) + rng.uniform(0, 1, (7, 3))) / K])
+    print(f"[multipoles] K={K}", flush=True)
+    b = nfp.bin_particles(torch.from_numpy(pos).to(DEV), K, 1.0, 1e-4)
+    got = nfp.multipoles(b, 0)
+    c = np.floor(pos * K).astype(np.int64)
+    cell, n = np.unique((c[:, 0] * K + c[:, 1]) * K + c[:, 2], return_counts=True)
+    assert int(torch.count_nonzero(got)) == len(cell)
+    np.testing.assert_array_equal(got[torch.from_numpy(cell).to(DEV), 0].cpu().numpy(), n)
+    del b, got
+    torch.cuda.empty_cache()
