@@ -70,32 +70,82 @@ constexpr int term_index(int a, int b, int c) {
 // first[w] = smallest c with cost(c) >= w kRange, for w = 0 .. nrange - 1,
 // and first[nrange] = ncell.  The pieces of each cell of more than kBig
 // particles, in order from wherever the count of pieces stands (total, zeroed
-// by the descriptor upload): no moment depends on the place.
-__global__ void __launch_bounds__(256)
+// by the descriptor upload): no moment depends on the place.  PER cells a
+// thread, NT apart.  A block draws from the count once, and a cell of many ranges
+// or pieces is written by its whole wave: strongly clustered, a draw and a thread
+// a big cell took 75 us of 16.8M particles' call, a draw per 256 cells 52 (and 392
+// of 134M), this 16 (72).
+template <int NT, int PER>
+__global__ void __launch_bounds__(NT)
 k_mp_plan(const DevBox *__restrict__ boxes, const int64_t *__restrict__ range_base,
           int32_t *__restrict__ first, uint32_t *__restrict__ total,
           MpPiece *__restrict__ pieces, int64_t max_pieces) {
     const DevBox &B = boxes[blockIdx.y];
+    const int64_t c0 = (int64_t)blockIdx.x * (NT * PER) + threadIdx.x;
+    if (c0 - threadIdx.x > B.ncell) return;   // whole workgroup
     int32_t *f = first + range_base[blockIdx.y] + blockIdx.y;   // nrange + 1 entries per box
     const int nrange = (int)(range_base[blockIdx.y + 1] - range_base[blockIdx.y]);
-    const int c = blockIdx.x * 256 + threadIdx.x;
-    if (c > B.ncell) return;
-    if (c == 0) {
-        f[0] = 0;
-        f[nrange] = B.ncell;
-    } else {
-        const int64_t lo = cell_cost(B.cell_start, c - 1) / kRange + 1;
-        const int64_t hi = cell_cost(B.cell_start, c) / kRange;
-        for (int64_t w = lo; w <= hi && w < nrange; ++w) f[w] = c;
+    const int lane = threadIdx.x & 63;
+    int q[PER], np[PER], n[PER], all = 0;
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        const int c = (int)min(c0 + i * NT, (int64_t)B.ncell);
+        int lo = 0, hi = -1;   // the ranges whose first cell is c
+        q[i] = n[i] = 0;
+        if (c0 + i * NT <= B.ncell) {
+            if (c == 0) {
+                f[0] = 0;
+                f[nrange] = B.ncell;
+            } else {
+                lo = (int)(cell_cost(B.cell_start, c - 1) / kRange) + 1;
+                hi = min((int)(cell_cost(B.cell_start, c) / kRange), nrange - 1);
+            }
+            if (c < B.ncell) {
+                q[i] = B.cell_start[c];
+                n[i] = B.cell_start[c + 1] - q[i];
+            }
+        }
+        if (hi - lo < 8)
+            for (int w = lo; w <= hi; ++w) f[w] = c;
+        for (uint64_t m = __ballot(hi - lo >= 8); m; m &= m - 1) {
+            const int l = __ffsll((unsigned long long)m) - 1;
+            const int a = __builtin_amdgcn_readlane(lo, l), b = __builtin_amdgcn_readlane(hi, l);
+            const int v = __builtin_amdgcn_readlane(c, l);
+            for (int w = a + lane; w <= b; w += 64) f[w] = v;
+        }
+        np[i] = n[i] > kBig ? (n[i] - 1) / kBig + 1 : 0;
+        all += np[i];
     }
-    if (c == B.ncell) return;
-    const int q = B.cell_start[c], n = B.cell_start[c + 1] - q;
-    if (n <= kBig) return;
-    const int np = (n + kBig - 1) / kBig;
-    const int64_t at = atomicAdd(total, (uint32_t)np);
-    for (int k = 0; k < np && at + k < max_pieces; ++k)
-        pieces[at + k] = MpPiece{(int32_t)blockIdx.y, c, q + k * kBig, min(q + n, q + (k + 1) * kBig),
-                                 k, np};
+    if (!__syncthreads_or(all)) return;
+    __shared__ uint32_t block_pieces, block_at;
+    if (threadIdx.x == 0) block_pieces = 0u;
+    __syncthreads();
+    int at = all ? (int)atomicAdd(&block_pieces, (uint32_t)all) : 0;
+    __syncthreads();
+    if (threadIdx.x == 0) block_at = atomicAdd(total, block_pieces);
+    __syncthreads();
+    at += (int)block_at;
+    auto put = [&](int64_t to, int cell, int q0, int cnt, int k, int k1) {
+        if (to + k < max_pieces)
+            pieces[to + k] = MpPiece{(int32_t)blockIdx.y, cell, q0 + k * kBig,
+                                     q0 + min(cnt, (k + 1) * kBig), k, k1};
+    };
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        const int c = (int)(c0 + i * NT);
+        if (np[i] <= 16)
+            for (int k = 0; k < np[i]; ++k) put(at, c, q[i], n[i], k, np[i]);
+        for (uint64_t m = __ballot(np[i] > 16); m; m &= m - 1) {
+            const int l = __ffsll((unsigned long long)m) - 1;
+            const int cell = __builtin_amdgcn_readlane(c, l);
+            const int q0 = __builtin_amdgcn_readlane(q[i], l);
+            const int cnt = __builtin_amdgcn_readlane(n[i], l);
+            const int k1 = __builtin_amdgcn_readlane(np[i], l);
+            const int to = __builtin_amdgcn_readlane(at, l);
+            for (int k = lane; k < k1; k += 64) put(to, cell, q0, cnt, k, k1);
+        }
+        at += np[i];
+    }
 }
 
 // The lanes' units for every order p: (a, b) pairs in order, each cut into
@@ -334,21 +384,33 @@ k_multipoles(const DevBox *__restrict__ boxes, int nbox, const int64_t *__restri
     }
 }
 
-// The first piece of each big cell adds the cell's pieces in order.
-__global__ void __launch_bounds__(64)
+// The first piece of each big cell adds the cell's pieces in order, a thread a
+// term, kAhead loads in flight: one by one they cost 0.9 us a piece.  16.8M strongly
+// clustered particles 193 -> 25 us; 2.1M in one cell 7.3 -> 0.4 ms a call.
+constexpr int kCombineThreads = 192;
+static_assert(kMaxTerms <= kCombineThreads, "a thread a term");
+__global__ void __launch_bounds__(kCombineThreads)
 k_mp_combine(const DevBox *__restrict__ boxes, const MpPiece *__restrict__ pieces,
              const uint32_t *__restrict__ total, const double *__restrict__ partial,
-             int nterms) {
-    const int w = blockIdx.x;
-    if (w >= (int64_t)*total) return;
-    const MpPiece pc = pieces[w];
-    if (pc.k != 0) return;
-    const DevBox &B = boxes[pc.box];
-    for (int t = threadIdx.x; t < nterms; t += 64) {
-        double sum = 0.0;
-        for (int k = 0; k < pc.np && w + k < (int)gridDim.x; ++k)
-            sum += partial[(int64_t)(w + k) * kMaxTerms + t];
-        gp(B.out)[(int64_t)pc.cell * nterms + t] = (float)sum;
+             int nterms, int64_t max_pieces) {
+    const int t = threadIdx.x;
+    if (t >= nterms) return;
+    constexpr int kAhead = 16;
+    const int all = (int)min((int64_t)*total, max_pieces);
+    for (int w = blockIdx.x; w < all; w += gridDim.x) {
+        const MpPiece pc = pieces[w];
+        if (pc.k != 0) continue;
+        const int np = min(pc.np, all - w);
+        const gptr<const double> from = gp(partial) + (int64_t)w * kMaxTerms + t;
+        double sum = 0.0, v[kAhead];
+        for (int k = 0; k < np; k += kAhead) {
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u) v[u] = from[(int64_t)min(k + u, np - 1) * kMaxTerms];
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u)
+                if (k + u < np) sum += v[u];
+        }
+        gp(boxes[pc.box].out)[(int64_t)pc.cell * nterms + t] = (float)sum;
     }
 }
 
@@ -383,7 +445,7 @@ constexpr bool grid_fits(int64_t n, int64_t ncell, int64_t nbox) {
     const int64_t pieces = 2 * (n / kBig) + nbox;
     const int64_t all = (n + kCellCost * ncell) / kRange + nbox + pieces;
     return grid_cols(all) * 64 < (int64_t)1 << 32 && grid_rows(all) < 65536 &&
-           grid_cols(all) * grid_rows(all) >= all && 64 * pieces < (int64_t)1 << 32;
+           grid_cols(all) * grid_rows(all) >= all && pieces <= INT32_MAX;
 }
 static_assert(grid_fits(0, 125, 1) && grid_fits(1 << 20, 1024 * 1024 * 1024, 1) &&
                   grid_fits(INT32_MAX, 1290 * 1290 * 1290, 1) &&
@@ -392,10 +454,17 @@ static_assert(grid_fits(0, 125, 1) && grid_fits(1 << 20, 1024 * 1024 * 1024, 1) 
 
 }  // namespace
 
+constexpr int64_t kFineCells = (int64_t)1 << 20;   // from here 4096 cells a planning block
+
 hipError_t multipole_launch(const DevBox *d_boxes, int nbox, const MpPlan &mp, int p,
                             hipStream_t s) {
-    hipLaunchKernelGGL(k_mp_plan, dim3((unsigned)((mp.max_ncell + 1 + 255) / 256), (unsigned)nbox),
-                       dim3(256), 0, s, d_boxes, mp.range_base, mp.first, mp.total, mp.pieces,
+    // The one count takes 87 M draws a second, so a block of a fine grid covers many
+    // cells; a coarse one would leave CUs idle (64^3 cells: 64 blocks).
+    const bool fine = mp.max_ncell >= kFineCells;
+    const int nt = fine ? 1024 : 256, per = fine ? 4 : 1;
+    hipLaunchKernelGGL((fine ? k_mp_plan<1024, 4> : k_mp_plan<256, 1>),
+                       dim3((unsigned)(mp.max_ncell / (nt * per) + 1), (unsigned)nbox), dim3(nt),
+                       0, s, d_boxes, mp.range_base, mp.first, mp.total, mp.pieces,
                        mp.max_pieces);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
@@ -405,9 +474,11 @@ hipError_t multipole_launch(const DevBox *d_boxes, int nbox, const MpPlan &mp, i
                        multipole_terms(p), (const MpPiece *)mp.pieces,
                        (const uint32_t *)mp.total, mp.max_pieces, mp.partial);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    hipLaunchKernelGGL(k_mp_combine, dim3((unsigned)std::max<int64_t>(1, mp.max_pieces)), dim3(64),
-                       0, s, d_boxes, (const MpPiece *)mp.pieces, (const uint32_t *)mp.total,
-                       (const double *)mp.partial, multipole_terms(p));
+    hipLaunchKernelGGL(k_mp_combine,
+                       dim3((unsigned)std::max<int64_t>(1, std::min<int64_t>(mp.max_pieces, 16384))),
+                       dim3(kCombineThreads), 0, s, d_boxes, (const MpPiece *)mp.pieces,
+                       (const uint32_t *)mp.total, (const double *)mp.partial, multipole_terms(p),
+                       mp.max_pieces);
     return hipGetLastError();
 }
 

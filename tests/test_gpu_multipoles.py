@@ -112,6 +112,21 @@ def test_multipoles_cells_around_chunk_run_and_piece_sizes(p):
     assert (nfp.multipoles(empty, p) == 0).all()
 
 
+@pytest.mark.parametrize("K", [6, 104])
+def test_multipoles_many_pieces_of_one_cell(K):
+    """Cells of 16, 17, 32, 33 and 79 pieces (a thread or its wave lists them,
+    16 at a time are added), the largest one first or last, on a coarse grid
+    and on one whose planning blocks cover 4096 cells."""
+    rng = np.random.default_rng(83)
+    cells = {0: 20000, 1: 4096, 2: 4097, K: 8192, K + 1: 8193, K ** 3 - 2: 257,
+             K ** 3 - 1: 20000, K ** 3 // 2: 300}
+    parts = [(np.array([c // K ** 2, c // K % K, c % K]) + rng.uniform(0, 1, (n, 3))) / K
+             for c, n in cells.items()]
+    pos = np.concatenate(parts + [rng.uniform(0, 1, (3000, 3))])
+    print(f"[multipoles] pieces K={K}", flush=True)
+    _check(pos[rng.permutation(len(pos))], K, 1.0, 2)
+
+
 def test_multipoles_of_uneven_boxes_equal_the_single_calls_bitwise():
     """A batch of empty, tiny, sparse, large and one-cell boxes in any order:
     every box's moments are those of the box alone."""
