@@ -60,17 +60,19 @@ constexpr int kRows = 25;            // (dx, dy) rows of the 5x5x5 block
 __device__ __forceinline__ int wrapk(int c, int K) { return c < 0 ? c + K : (c >= K ? c - K : c); }
 __device__ __forceinline__ int uni(int x) { return __builtin_amdgcn_readfirstlane(x); }
 
-// log2 of the consecutive items that stay on one XCD: `most`, or less so that
-// every XCD gets at least eight blocks (blocks of 256 left 463 light items on
-// two of the eight XCDs).
-__device__ __forceinline__ int xcd_block_log2(int nitems, int most) {
+// The place of an item in its block, as a mask: a block is the consecutive items
+// that stay on one XCD, `most` (a power of two), or less so that every XCD gets at
+// least eight blocks (blocks of 256 left 463 light items on two of the eight XCDs).
+__device__ __forceinline__ int xcd_block_mask(int nitems, int most) {
     int b = 31 - __builtin_clz(most);
     while (b > 0 && nitems < 8 * kXcds << b) --b;
-    return b;
+    return (1 << b) - 1;
 }
-// Item number of claim t of XCD x's queue: XCD x takes the blocks x, x + 8, ...
-__device__ __forceinline__ int xcd_item(int t, int x, int b) {
-    return ((((t >> b) * kXcds) + x) << b) + (t & ((1 << b) - 1));
+// Item number of claim t of XCD x's queue: XCD x takes the items of the blocks x,
+// x + 8, ... in order.  (Shifts by the block's logarithm instead took two to
+// four vector registers more, which cost the narrow kernels a wave per SIMD.)
+__device__ __forceinline__ int xcd_item(int t, int x, int mask) {
+    return t + (t & ~mask) * (kXcds - 1) + x * (mask + 1);
 }
 
 // Inclusive prefix sums over the lanes of a wave (all 64 lanes active): a
@@ -646,14 +648,14 @@ __device__ __forceinline__ void dense_items(const int lane, const DevBox *__rest
     // the heaviest items still come first everywhere (the map is one-to-one
     // and increasing, so only the locality depends on the placement)
     const int x = (int)(blockIdx.x % kXcds);
-    const int xb = xcd_block_log2(nitems, kDenseBlock);
+    const int mask = xcd_block_mask(nitems, kDenseBlock);
     uint32_t *dq = counter + kQueueStride * x;
     for (;;) {
         int t = 0;
         if (lane == 0)
             t = (int)__hip_atomic_fetch_add(gp(dq), 1u, __ATOMIC_RELAXED,
                                             __HIP_MEMORY_SCOPE_AGENT);
-        const int itx = xcd_item(uni(t), x, xb);
+        const int itx = xcd_item(uni(t), x, mask);
         if (itx >= nitems) break;
         const gptr<const Item> ip = gp(items) + itx;
         const Item I{ip->box, ip->cell0, ip->m, ip->chunk};
@@ -1209,10 +1211,11 @@ __device__ __forceinline__ void light_items(LightSmem<MODE, CAP, NT> &sm, const 
     // so the results do not depend on where the workgroups actually run;
     // only the L2 locality does.
     uint32_t *qc = counter + kQueueStride * q;
-    const int xb = xcd_block_log2(nitems, kXcdBlock);
-    auto queue_item = [q, xb](int kth) {
+    const int x = q % kXcds, nth = q / kXcds;
+    const int mask = xcd_block_mask(nitems, kXcdBlock);
+    auto queue_item = [x, nth, mask](int kth) {
         // the XCD's t-th item
-        return xcd_item(kth * (kQueues / kXcds) + q / kXcds, q % kXcds, xb);
+        return xcd_item(kth * (kQueues / kXcds) + nth, x, mask);
     };
     if (lane == 0) {
         const int first = queue_item((int)__hip_atomic_fetch_add(gp(qc), 1u, __ATOMIC_RELAXED,
@@ -1245,10 +1248,11 @@ __device__ __forceinline__ void light_items(LightSmem<MODE, CAP, NT> &sm, const 
         const int g = min(uni(cs[cell0 + 1]) - s0, kUnit);
 
         // ---- this lane's sink (sink a, source slice b), loaded before the setup
-        Coef k{B.cA, B.cB, B.cC, 2.0f * B.cC, B.eps * B.eps, B.r2floor};
-        // the plain VJP has no register to spare for it (1.8M particles, light items
-        // alone: 983 us with, 940 without)
-        if constexpr (MODE == 0 || COMP) in_vector(k.floor);
+        // (the floor stays in a scalar register: in a vector one it costs the narrow
+        // kernels a wave per SIMD, and putting it there waits for it before the item's
+        // loads are issued.  4.2M particles plain 1956 / 1888 us, compensated VJP
+        // 3245 / 3057)
+        const Coef k{B.cA, B.cB, B.cC, 2.0f * B.cC, B.eps * B.eps, B.r2floor};
         const bool fast = B.outer_newton != 0;
         const int flush = uni(B.flush);
         const int P = NT / g;
