@@ -743,12 +743,17 @@ __device__ __forceinline__ void dense_items(const int lane, const DevBox *__rest
     }
 }
 
+// Workgroups from the cap on leave at once where there are many items
+// (launch_dense).
+constexpr int kCapItems = 2048;
 template <int MODE, bool COMP>
 __global__ void __launch_bounds__(kUnit)
 k_dense(const DevBox *__restrict__ boxes, const Item *__restrict__ items,
         const uint32_t *__restrict__ totals, uint32_t *counter,
-        const float4 *__restrict__ cot_sorted) {
-    dense_items<MODE, COMP>((int)threadIdx.x, boxes, items, (int)totals[0], counter, cot_sorted);
+        const float4 *__restrict__ cot_sorted, int cap) {
+    const int nitems = (int)totals[0];
+    if ((int)blockIdx.x >= cap && nitems >= kCapItems) return;
+    dense_items<MODE, COMP>((int)threadIdx.x, boxes, items, nitems, counter, cot_sorted);
 }
 
 // ------------------------------------------------------------------ dense path, few items
@@ -1740,17 +1745,22 @@ hipError_t launch_dense(const DevBox *d_boxes, const TilePlan &tp, const float4 
     // they do in the largest boxes, they need all.  Full / capped, clustered, us:
     // accelerations 1M 762 / 739, 2.1M 1391 / 1365, 4M 2532 / 2506 (more clustered
     // 3266 / 3232, 8M 6755 / 7082); VJP 1M 1134 / 1077, 2.1M 2186 / 2161, 4M 4173 /
-    // 4203.  Every XCD queue needs at least one workgroup: a multiple of kXcds.
-    const bool cap =
-        concurrent && !f4 && tp.particles <= (MODE == 0 ? kDenseCapAccel : kDenseCapVjp);
+    // 4203.  Not with fewer than kCapItems items: a short dense kernel on few waves
+    // lets the light kernels start together, and their workgroups then share the CUs
+    // unevenly (full / capped, compensated: 1M uniform of 0.5 a cell 1015 / 1083, 2M
+    // of 3.5 a cell 1005 / 1071, 4M of 5 a cell 1789 / 1904).  Every XCD queue needs at
+    // least one workgroup: multiples of kXcds.
     static const int full =
         (persistent_grid(k_dense<MODE, COMP>, kUnit) + kXcds - 1) / kXcds * kXcds;
-    static const int capped =
+    static const int few =
         (persistent_grid(k_dense<MODE, COMP>, kUnit, MODE == 0 ? 12 : 16) + kXcds - 1) / kXcds *
         kXcds;
-    const int grid = grid_for(cap ? capped : full, tp.max_dense, kXcds);
+    const int grid = grid_for(full, tp.max_dense, kXcds);
+    const bool capped =
+        concurrent && !f4 && tp.particles <= (MODE == 0 ? kDenseCapAccel : kDenseCapVjp);
     hipLaunchKernelGGL((k_dense<MODE, COMP>), dim3(grid), dim3(kUnit), 0, s, d_boxes,
-                       (const Item *)tp.dense, (const uint32_t *)tp.totals, tp.counter, cot);
+                       (const Item *)tp.dense, (const uint32_t *)tp.totals, tp.counter, cot,
+                       capped ? few : grid);
     return hipGetLastError();
 }
 
