@@ -197,8 +197,13 @@ k_plan_count(const DevBox *__restrict__ boxes, uint32_t *cellinfo, uint32_t *buc
 // Heavy dense items, the first of the list: those of more than 1 / share of all
 // dense items' sources, which one wave each would still be summing when the rest
 // of the call is done.  A lane's buckets b0 and b0 - 1 hold c0 and c1 items.
-// Shares measured at 262k particles, us: accelerations 500 / 1000 / 2000: 340 /
-// 264 / 331; VJP 1000 / 1400 / 2000 / 4000: 473 / 412 / 436 / 463.
+// Whole calls with half the share / this / twice, us, of clustered boxes (particles a
+// cell and spread of ln density 8 and 1.0; 8 and 1.5; 8 and 2.0; 14 and 1.5): plain 100k 131 / 132 / 131, 170 / 173 / 176,
+// 291 / 221 / 240, 272 / 222 / 238; 200k 195 / 198 / 199, 315 / 285 / 306, 351 / 333 / 352,
+// 363 / 329 / 383; 340k 262 / 275 / 275, 352 / 300 / 322, 496 / 471 / 428, 543 / 487 / 494.
+// Compensated VJP 100k 187 / 186 / 187, 269 / 251 / 253, 436 / 341 / 351, 420 / 346 / 347; 200k
+// 290 / 292 / 292, 559 / 450 / 460, 952 / 522 / 516, 724 / 543 / 583; 340k 405 / 405 / 404, 614 /
+// 503 / 525, 1034 / 825 / 763, 1082 / 831 / 845.
 constexpr float kHeavyShareAccel = 1000.0f, kHeavyShareVjp = 1400.0f;
 __device__ __forceinline__ uint32_t heavy_items(int b0, int c0, int c1, float share) {
     const float s0 = exp2f(0.25f * (float)b0), s1 = exp2f(0.25f * (float)(b0 - 1));
@@ -1071,6 +1076,13 @@ k_dense_wide(const DevBox *__restrict__ boxes, const Item *__restrict__ items,
     __shared__ WideSmem<kProducers> sm;
     const int nitems = (int)totals[0], heavy = (int)totals[3];
     wide_items<MODE, COMP, kProducers>(sm, boxes, items, heavy, counter, cot_sorted);
+    // Nothing heavy: all items are alike, or few.  A workgroup's waves then claim one
+    // after another (1.3 us apart), so that the first waves of all workgroups take
+    // the largest items; else the workgroups that start first took eight each and
+    // left CUs idle.  Uniform, compensated VJP, us: 100k particles of 463 a cell 11200
+    // / 6250, 262k of 152 a cell 4880 / 3670; accelerations 4590 / 3470, 2200 / 1900.
+    if (heavy == 0)
+        for (int i = uni(threadIdx.x >> 6); i > 0; --i) __builtin_amdgcn_s_sleep(48);
     dense_items<MODE, COMP>((int)(threadIdx.x & 63), boxes, items + heavy, nitems - heavy,
                             counter + 1, cot_sorted);
 }
@@ -1717,11 +1729,14 @@ hipError_t launch_narrow(const DevBox *d_boxes, const TilePlan &tp, const float4
 
 // k_dense_wide takes the dense items of calls of at most this many particles
 // (over all boxes): above, the card is full with one wave an item and nothing
-// waits for the heaviest one.  Whole force calls with k_dense / k_dense_wide,
-// clustered boxes, us: 65k particles plain 285 / 180, VJP 500 / 233; 131k 245 / 206,
-// 433 / 284; 262k 304 / 264, 596 / 412; 400k 393 / 402, 719 / 601; 524k 483 / 486,
-// 887 / 727; 700k 562 / 569, 845 / 876; 1M 775 / 759, 1144 / 1169.
-constexpr int64_t kWideMaxAccel = 350000, kWideMaxVjp = 600000;
+// waits for the heaviest one.  Whole force calls with k_dense / k_dense_wide, us, of
+// the boxes named at kHeavyShareAccel: plain 100k 140 / 132, 228 / 173, 325 / 221, 252 / 222; 200k 188 / 198, 462 /
+// 285, 388 / 333, 339 / 329; 340k 248 / 275, 286 / 300, 509 / 471, 556 / 487.
+// Compensated VJP 200k 357 / 292, 927 / 450, 773 / 522, 694 / 543; 340k 398 / 405, 521 /
+// 503, 1069 / 825, 1094 / 831; 420k 461 / 496, 820 / 655, 894 / 897, 1049 / 1255; 500k
+// 566 / 572, 598 / 708, 1491 / 1242, 1323 / 1450; 590k 595 / 624, 764 / 790, 1581 / 1541,
+// 1088 / 1244 (another draw of 8 and 1.5: 420k 608 / 564, 590k 962 / 794).
+constexpr int64_t kWideMaxAccel = 350000, kWideMaxVjp = 450000;
 constexpr int64_t kDenseCapAccel = 5000000, kDenseCapVjp = 2500000;   // see launch_dense
 
 template <int MODE, bool COMP>
