@@ -102,6 +102,7 @@ struct Layout {
     size_t mp_total_off = 0, mp_pieces_off = 0, mp_partial_off = 0;
     int64_t mp_max_pieces = 0;
     int64_t max_dense = 0;
+    double uniform_pairs = 0;   // sum over the boxes of 125 n^2 / K^3
     size_t accel_end = 0;   // bytes an accelerations call uses (table + planner)
     // pair symmetry (flag NF_PAIR_SYMMETRIC), after the planner's tables
     size_t f4P_off = 0, f4nf_off = 0, f4slot_off = 0, f4item_cnt_off = 0, f4scan_off = 0,
@@ -167,6 +168,7 @@ int validate(int nbox, const nf_box *boxes, Layout &L, uint32_t flags = 0) {
         const int dm = B.dense_min ? B.dense_min : kDefaultDenseMin;
         L.max_dense += B.n / std::min(dm, 64) + 1;
         L.max_ncell = std::max<int64_t>(L.max_ncell, ncell);
+        L.uniform_pairs += 125.0 * (double)B.n * (double)B.n / (double)ncell;
     }
     if (L.N > INT32_MAX) return fail(NF_EUNSUPPORTED, "total particles over all boxes exceed 2^31 - 1");
     if (L.C + 1 > INT32_MAX) return fail(NF_EUNSUPPORTED, "total cells over all boxes exceed 2^31 - 2");
@@ -454,6 +456,7 @@ static TilePlan tile_plan(const Layout &L, char *w) {
     tp.TG = L.C;
     tp.max_cells = L.max_ncell;
     tp.particles = L.N;
+    tp.uniform_pairs = L.uniform_pairs;
     tp.max_dense = L.max_dense;
     tp.max_light = std::max<int64_t>(1, std::min(L.C, L.N));
     tp.cellinfo = reinterpret_cast<uint32_t *>(w + L.cellinfo_off);

@@ -66,6 +66,7 @@ struct TilePlan {
     int64_t TG = 0;              // cells over all boxes (planning is per cell)
     int64_t max_cells = 0;       // largest per-box cell count
     int64_t particles = 0;       // particles over all boxes
+    double uniform_pairs = 0;    // pairs that uniform boxes of these sizes would form
     int64_t max_dense = 0;       // bound on the dense items
     int64_t max_light = 0;       // bound on the light items, and on the narrow ones
     uint32_t *cellinfo = nullptr;     // [TG] item kind and cost bucket per cell

@@ -1779,14 +1779,20 @@ hipError_t launch_dense(const DevBox *d_boxes, const TilePlan &tp, const float4 
     return hipGetLastError();
 }
 
-// k_small takes calls of at most this many particles (with the default windows,
-// which it is built for).  Below, a call is bound by the host: a fork to two
-// streams and the joins take 50 us of it.  Above, a workgroup per CU is too few
-// for the dense items.  Whole calls, three kernels on three streams / k_small,
-// us, clustered: 1000 particles plain 82 / 28, VJP 65 / 37; 4096 92 / 47, 103 /
-// 52; 50k 133 / 122, 176 / 167 (compensated 134 / 140, 183 / 183); 65k 179 / 173,
-// 234 / 232 (compensated 174 / 202, 246 / 271); 100k 184 / 217, 269 / 297; uniform
-// 32768 89 / 56, 107 / 80.
+// k_small takes small calls (with the default windows, which it is built for): they
+// are bound by the host, and a fork to two streams and the joins take 50 us of it.
+// Small is at most kSmallOne particles, a full dense chunk for every CU, or at most
+// kSmallMax of which uniform boxes would form at most kSmallPairs pairs: with more
+// work, one workgroup a CU is too few for the dense items.  Whole calls, three
+// kernels / k_small, us, plain, compensated and compensated VJP: 1000 particles 67 /
+// 27, 67 / 28, 70 / 38; 10k of 80 a cell 270 / 181, 261 / 231, 342 / 257; 40k of 8 a
+// cell (4e7 pairs) uniform 84 / 56, 87 / 59, 109 / 84, spread of ln density 1.5 101 / 89,
+// 102 / 99, 139 / 133; of 14 (7e7) 149 / 161, 146 / 183, 209 / 244; 59k of 8 (6e7) uniform 95 /
+// 67, 98 / 71, 125 / 101, spread 1.5 130 / 131, 136 / 151, 187 / 199; of 14 (1e8) 175 / 192,
+// 181 / 223, 251 / 292; of 44 (3e8) uniform 380 / 464, 391 / 559, 550 / 724 (414, 437, 797
+// before there was either).
+constexpr int64_t kSmallOne = 16384;
+constexpr double kSmallPairs = 6.5e7;
 constexpr int64_t kSmallMax = 60000;
 
 template <int MODE, bool COMP>
@@ -1812,7 +1818,9 @@ hipError_t launch_force(const DevBox *d_boxes, const TilePlan &tp, const float4 
         if (f4 && (e = f4_ring_launch(d_boxes, *f4, COMP, s)) != hipSuccess) return e;
         return hipSuccess;
     }
-    if (!f4 && tp.particles <= kSmallMax && tp.light_window == kDefaultLightWindow &&
+    const bool small = tp.particles <= kSmallOne ||
+                       (tp.particles <= kSmallMax && tp.uniform_pairs <= kSmallPairs);
+    if (!f4 && small && tp.light_window == kDefaultLightWindow &&
         tp.narrow_window == kDefaultNarrowWindow)
         return launch_small<MODE, COMP>(d_boxes, tp, cot, s);
     std::lock_guard<std::mutex> lk(g_side_mu);

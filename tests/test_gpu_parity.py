@@ -420,6 +420,21 @@ def test_small_call_in_one_launch_equals_the_separate_kernels_bitwise(counts):
                                    nfp.accel_vjp(b, v, 1.0, serial=True, **kw))
 
 
+@pytest.mark.parametrize("n,K", [(16384, 5), (16385, 5), (20000, 14), (60000, 19), (60000, 13),
+                                 (60001, 60)])
+def test_calls_around_the_limits_of_the_single_launch_bitwise(n, K):
+    """Small calls and small calls of much work, on both sides of the rule that
+    picks the single kernel: the separate kernels in turn give the same bits."""
+    b = nfp.bin_particles(_gpu(uniform_box(n, 1.0, seed=n)), K, 1.0, 0.2 / K)
+    v = torch.from_numpy(gaussian_cotangent(n, 33).astype(np.float32)).to(DEV)
+    for comp in (False, True):
+        print(f"[limits] {n} {K} {comp}", flush=True)
+        assert torch.equal(nfp.accel(b, 1.0, compensated=comp),
+                           nfp.accel(b, 1.0, compensated=comp, serial=True))
+        assert torch.equal(nfp.accel_vjp(b, v, 1.0, compensated=comp),
+                           nfp.accel_vjp(b, v, 1.0, compensated=comp, serial=True))
+
+
 def test_tile_all_items_narrow():
     """A sparse box (at most 11 particles per cell): every item is narrow and
     the dense and light kernels find empty queues."""
