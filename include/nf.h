@@ -131,6 +131,7 @@ enum {
  *               large that s = x K / L has magnitude >= 2^62.  Such particles
  *               are binned into cell 0 at offset 0 and every force computed
  *               for that box is then meaningless; the caller must check it.
+ *               Boxes of a call may share the word: it then holds their sum.
  * Requirements: n >= 0, 5 <= K (K = 2R+1 with R = 2; smaller grids would
  * alias the 5x5x5 block), K^3 + 1 <= 2^31 - 1, n <= 2^31 - 1, L and eps_s
  * finite and > 0.  Pointers may be NULL only when n == 0 (cell_start never).

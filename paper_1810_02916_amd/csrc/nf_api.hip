@@ -1,5 +1,6 @@
 // nf_api.hip -- host side of the C ABI declared in include/nf.h: argument
 // validation, workspace layout, descriptor upload and kernel dispatch.
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -292,6 +293,16 @@ int check_ws(const Layout &L, void *ws, size_t ws_bytes) {
     return NF_OK;
 }
 
+// Do boxes share a word nbad?  It then holds the sum over them.
+bool nbad_shared(int nbox, const nf_box *boxes) {
+    if (nbox < 2) return false;
+    std::vector<const int32_t *> p;
+    for (int b = 0; b < nbox; ++b)
+        if (boxes[b].nbad) p.push_back(boxes[b].nbad);
+    std::sort(p.begin(), p.end());
+    return std::adjacent_find(p.begin(), p.end()) != p.end();
+}
+
 void fill_geometry(const nf_box &B, const Layout &L, int b, DevBox &d, bool plummer = false,
                    bool no_shortcut = false) {
     std::memset(&d, 0, sizeof d);
@@ -410,7 +421,8 @@ int nf_bin_particles(int nbox, const nf_box *boxes, void *ws, size_t ws_bytes, v
         hipStream_t s = static_cast<hipStream_t>(stream);
         char *w = static_cast<char *>(ws);
         DevBox *d_tab = reinterpret_cast<DevBox *>(w + L.table_off);
-        const bool small = bin_is_small(L.max_n, L.max_ncell);
+        const bool shared_bad = nbad_shared(nbox, boxes);
+        const bool small = bin_is_small(L.max_n, L.max_ncell) && !shared_bad;
         const bool in_args = small && tab_bytes <= (size_t)kChunkBytes;
         hipError_t e = in_args ? hipSuccess
                                : upload(tab.data(), tab_bytes, d_tab, s,
@@ -433,6 +445,7 @@ int nf_bin_particles(int nbox, const nf_box *boxes, void *ws, size_t ws_bytes, v
         p.pitch = L.pitch;
         p.passes = L.passes;
         p.radix_bits = L.radix_bits;
+        p.shared_bad = shared_bad;
         for (int k = 0; k < 2; ++k) {
             p.sc.keys[k] = reinterpret_cast<uint32_t *>(w + L.keys_off[k]);
             p.sc.rec[k] = reinterpret_cast<float4 *>(w + L.rec_off[k]);

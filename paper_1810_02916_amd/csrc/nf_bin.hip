@@ -676,6 +676,16 @@ hipError_t bin_small_launch(const Chunk &c, const DevBox *d_boxes, int nbox, hip
     return hipGetLastError();
 }
 
+// Boxes that share their word nbad: each writes the sum over its sharers.
+__global__ void __launch_bounds__(256)
+k_bin_shared_bad(const DevBox *__restrict__ boxes, int nbox, const uint32_t *__restrict__ bad) {
+    const int b = blockIdx.x * 256 + threadIdx.x;
+    if (b >= nbox || !boxes[b].nbad) return;
+    uint32_t sum = 0;
+    for (int q = 0; q < nbox; ++q) sum += boxes[q].nbad == boxes[b].nbad ? bad[q] : 0u;
+    boxes[b].nbad[0] = (int32_t)sum;
+}
+
 hipError_t bin_launch(const DevBox *d_boxes, int nbox, const BinPlan &p, hipStream_t s) {
     hipError_t e;
     if (p.N > 0) {
@@ -686,6 +696,9 @@ hipError_t bin_launch(const DevBox *d_boxes, int nbox, const BinPlan &p, hipStre
     hipLaunchKernelGGL(k_bin_cells, dim3((unsigned)(p.max_n / 256 + 1), (unsigned)nbox), dim3(256),
                        0, s, d_boxes, (const uint32_t *)p.sc.keys[p.passes & 1],
                        (const uint32_t *)p.sc.bad);
+    if ((e = hipGetLastError()) != hipSuccess || !p.shared_bad) return e;
+    hipLaunchKernelGGL(k_bin_shared_bad, dim3((unsigned)(nbox + 255) / 256), dim3(256), 0, s,
+                       d_boxes, nbox, (const uint32_t *)p.sc.bad);
     return hipGetLastError();
 }
 

@@ -26,6 +26,7 @@ struct BinPlan {
     int64_t pitch = 0;      // words per row of the tile histograms
     int passes = 0;         // radix passes covering keys 0..C-1 (at least 1)
     int radix_bits = 8;     // digit width: 8, or 9 when that saves a pass
+    bool shared_bad = false;   // some boxes share their word nbad
     BinScratch sc{};
 };
 

@@ -140,6 +140,26 @@ def test_bin_routes_bit_exact(Ks, ns):
         assert bx.off.cpu().numpy().tobytes() == off.tobytes()
 
 
+@pytest.mark.parametrize("ns", [(300, 0, 40, 7), (9000, 0, 5000, 7)])
+def test_boxes_may_share_the_count_of_bad_positions(ns):
+    """One word for several boxes (small ones, and ones that the tiled sort
+    takes) holds the sum of their bad particles, in every call anew; a box with
+    a word of its own has its own count there."""
+    rng = np.random.default_rng(45)
+    pos = [rng.uniform(0, 1, (n, 3)) for n in ns]
+    for k, x in enumerate(pos):
+        x[:k + 1, k % 3] = np.nan
+    b = nfp.bin_particles_batched([_gpu(x) for x in pos], [6, 5, 7, 5], [1.0] * 4, [0.01] * 4,
+                                  check=False)
+    for k in (1, 2):
+        b.boxes[k].nbad = b.boxes[0].nbad
+    b._arr = None
+    for _ in range(2):
+        assert nfp.rebin(b, check=False).nbad() == [4, 4, 4, 4]
+    b.boxes[0].pos[0] = 0.5
+    assert nfp.rebin(b, check=False).nbad() == [3, 3, 3, 4]
+
+
 def test_bin_batched_matches_single():
     specs = batched_specs(4, seed=5, lo=4000, hi=9000)
     poss = [make_box(s) for s in specs]
