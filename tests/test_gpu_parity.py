@@ -416,6 +416,73 @@ def test_dense_items_of_small_and_large_calls_bitwise(law):
                                nfp.accel_vjp(two, [v, torch.ones_like(far).float()], 1.0, **kw)[0])
 
 
+def _heavy_items(pos, K, share):
+    """(dense items, those of them that a workgroup sums) of a box in cells of unit
+    box K^3: items of more than 1 / share of all items' sources, each counted as
+    the lower end of its quarter octave of sources."""
+    c = np.floor(pos * K).astype(np.int64)
+    n = np.bincount((c[:, 0] * K + c[:, 1]) * K + c[:, 2], minlength=K ** 3).reshape(K, K, K)
+    items = n // 64 + (n % 64 >= 41)
+    S = n
+    for ax in range(3):
+        S = sum(np.roll(S, d, axis=ax) for d in range(-2, 3))
+    low = 2.0 ** (np.floor(4.0 * np.log2(np.maximum(S, 1))) / 4.0)
+    return items.sum(), items[low > (items * low).sum() / share].sum()
+
+
+@pytest.mark.parametrize("law", ["spline", "wide spline", "plummer"])
+def test_dense_items_of_one_wave_and_of_a_workgroup_bitwise(law):
+    """Cells of 0..5 sources, remainders and empty groups, as in the test above,
+    in a small call (a workgroup an item) and beside a box that makes the call
+    one of single waves for the VJP as well as the accelerations."""
+    K, L = 6, 1.0
+    pos = _gpu(_box_with_counts(K, L, [2, 0, 3, 65, 4, 1, 5, 33, 0, 66, 64, 7, 129], seed=21))
+    far = _gpu(uniform_box(650000, L, seed=22))
+    eps = (1.7 if law == "wide spline" else 0.2) * L / K
+    v = torch.from_numpy(gaussian_cotangent(len(pos), 23).astype(np.float32)).to(DEV)
+    one = nfp.bin_particles(pos, K, L, eps)
+    two = nfp.bin_particles_batched([pos, far], [K, 44], [L, L], [eps, 0.01])
+    for flush in (0, 1, 5, 33):
+        one.set_tiles(nfp.Tiles(dense_min=2, flush=flush))
+        two.set_tiles(nfp.Tiles(dense_min=2, flush=flush))
+        for comp in (False, True):
+            print(f"[dense] {law} flush {flush} comp {comp}", flush=True)
+            kw = dict(compensated=comp, plummer=law == "plummer")
+            assert torch.equal(nfp.accel(one, 1.0, **kw), nfp.accel(two, 1.0, **kw)[0])
+            assert torch.equal(nfp.accel_vjp(one, v, 1.0, **kw),
+                               nfp.accel_vjp(two, [v, torch.ones_like(far).float()], 1.0, **kw)[0])
+
+
+@pytest.mark.parametrize("clump", [12000, 0])
+def test_heavy_and_other_dense_items_in_one_call_bitwise(clump):
+    """A middle-sized call with heavy and other dense items (a cell of 12000
+    among cells of 50), or with items that are all alike, against the same box
+    beside a filler that makes the call one of single waves."""
+    K, n = 12, 86000
+    rng = np.random.default_rng(46)
+    pos = rng.uniform(0, 1, (n, 3))
+    pos[:clump] = (np.array([3, 11, 0]) + rng.uniform(0, 1, (clump, 3))) / K
+    pos = pos[rng.permutation(n)]
+    for share in (1000, 1400):
+        items, heavy = _heavy_items(pos, K, share)
+        assert (0 < heavy < items) if clump else (items > 0 and heavy == 0)
+    one = nfp.bin_particles(_gpu(pos), K, 1.0, 0.02)
+    far = _gpu(uniform_box(600000, 1.0, seed=47))
+    two = nfp.bin_particles_batched([_gpu(pos), far], [K, 42], [1.0, 1.0], [0.02, 0.01])
+    v = torch.from_numpy(gaussian_cotangent(n, 48).astype(np.float32)).to(DEV)
+    for plummer in (False, True):
+        for comp in (False, True):
+            print(f"[heavy] {clump} {plummer} {comp}", flush=True)
+            kw = dict(compensated=comp, plummer=plummer)
+            a, g = nfp.accel(one, 1.0, **kw), nfp.accel_vjp(one, v, 1.0, **kw)
+            assert torch.equal(a, nfp.accel(two, 1.0, **kw)[0])
+            assert torch.equal(g, nfp.accel_vjp(two, [v, torch.ones_like(far).float()], 1.0,
+                                                **kw)[0])
+            assert torch.equal(a, nfp.accel(one, 1.0, serial=True, **kw))
+            assert torch.equal(g, nfp.accel_vjp(one, v, 1.0, serial=True, **kw))
+            assert torch.equal(a, nfp.accel_noalloc(one, 1.0, **kw))
+
+
 @pytest.mark.parametrize("counts", [
     [0] * 124 + [1], [3, 0, 11], [12, 40, 0, 25], [41, 64, 128],
     [0, 1, 2, 5, 11, 12, 40, 41, 63, 64, 65, 76, 139, 700]],
