@@ -72,7 +72,7 @@ struct TilePlan {
     int64_t max_light = 0;       // bound on the light items, and on the narrow ones
     uint32_t *cellinfo = nullptr;     // [TG] item kind and cost bucket per cell
     uint32_t *bucket_cnt = nullptr;   // [plan_buckets()] items per (kind, bucket), fill cursors
-    uint32_t *totals = nullptr;  // [3] dense, light and narrow item counts
+    uint32_t *totals = nullptr;  // [4] dense, light and narrow item counts, heavy dense items
     Item *dense = nullptr;       // dense items, heaviest first
     Item *light = nullptr;       // light items, then narrow items, each in spatial slabs
     uint32_t *counter = nullptr; // [queue_words()] queue counters

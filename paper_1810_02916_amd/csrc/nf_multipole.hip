@@ -2,9 +2,9 @@
 // four consecutive powers z^c0 .. z^(c0+3) of the same (a, b), so its terms
 // share one product x^a (y^b z^c0), each added by one fused multiply-add with
 // z^0 .. z^3 (61 units cover the 165 terms of order 8).  Particles are staged
-// 64 at a time: double x^k and y^b z^c0 in LDS, one row per power, z in the
-// lane's register (the next 64 offsets are loaded while the current ones are
-// summed).
+// kChunk = 32 at a time: double x^k and y^b z^c0 in LDS, one row per power, z in
+// the lane's register.  In a run the offsets of kBatch = 4 chunks are loaded
+// together, in a piece those of the next chunk while the current one is summed.
 //
 //   k_mp_plan     the first cell of every run, and the pieces of the big cells
 //   k_multipoles  a run of consecutive cells of bounded cost (particles plus
@@ -19,13 +19,15 @@
 // Every moment is a fixed sequence of double operations, so the moments are
 // reproducible.
 //
-// Bound by VALU issue (counted: 16 operations a particle, 9 of them its sums,
-// the rest staging and stores): a particle takes 17 clocks of a CU there and 9
-// of LDS; with the four z powers read from LDS too that was 24 and set the time.
+// Bound by FP64 issue for about 60 % of the time (counted, 2.1M particles: 15.5 VALU
+// instructions a particle, 9 of them its sums, at 4.4 clocks of a SIMD; it spends
+// 7.4 on one, with 3.8 waves a SIMD, the rest waiting for LDS, stores and
+// barriers).  A particle takes 9 clocks of a CU of LDS; with the four z powers read
+// from LDS too that was 24 and set the time.
 // 6 KB of LDS a workgroup, so that registers limit the waves (five per SIMD), and
 // short runs, so that the last ones even out.  64^3 cells, 2.1M clustered
-// particles, order 8 (173 MB of moments), the whole call: 151 -> 110 us; 50k
-// particles of 18^3 cells 45 -> 25.
+// particles, order 8 (173 MB of moments), the whole call: 151 -> 107 us; 50k
+// particles of 18^3 cells 45 -> 28.
 #include "nf_internal.h"
 #include "nf_kernels.h"
 
