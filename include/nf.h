@@ -202,7 +202,7 @@ size_t nf_workspace_bytes(int nbox, const nf_box *boxes, uint32_t flags);
  * Binning (Sec. 2.1): for each box, assign every particle to its cell,
  * compute its centre offset, and sort particles by cell (stable).
  * Writes off, cell_start, order (and nbad) of every box.
- * Work: about 70 bytes of HBM traffic per particle in the first radix pass (the
+ * Work: about 75 bytes of HBM traffic per particle in the first radix pass (the
  * positions are read twice), 45 in each later one.
  */
 int nf_bin_particles(int nbox, const nf_box *boxes, void *ws, size_t ws_bytes,
